@@ -49,12 +49,14 @@ template <> struct Normal4<double> {
                                                uint32_t c3, double z[4]) {
         U4 r = philox(seed, c0, c1, c2, c3);
         const double scale = 1.0 / 4294967296.0;
-        const double two_pi = 6.283185307179586476925286766559;
         double ua = ((double)r.x + 0.5) * scale, ub = ((double)r.y + 0.5) * scale;
         double uc = ((double)r.z + 0.5) * scale, ud = ((double)r.w + 0.5) * scale;
         double ra = sqrt(-2.0 * log(ua)), rc = sqrt(-2.0 * log(uc));
-        z[0] = ra * cos(two_pi * ub); z[1] = ra * sin(two_pi * ub);
-        z[2] = rc * cos(two_pi * ud); z[3] = rc * sin(two_pi * ud);
+        double sb, cb, sd, cd;
+        sincospi(2.0 * ub, &sb, &cb);
+        sincospi(2.0 * ud, &sd, &cd);
+        z[0] = ra * cb; z[1] = ra * sb;
+        z[2] = rc * cd; z[3] = rc * sd;
     }
 };
 
@@ -86,13 +88,14 @@ template <> struct Normal6<double> {
         const U4 r = philox(seed, c0, c1, c2, c3);
         const uint32_t a[6] = {r.x >> 11, r.y >> 11, r.z >> 11, r.w >> 11, ((r.x & 0x7ffu) << 10) | (r.y & 0x3ffu),
                                ((r.z & 0x7ffu) << 10) | (r.w & 0x3ffu)};
-        const double two_pi = 6.283185307179586476925286766559;
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
             const double ua = ((double)a[2 * p] + 0.5) * 0x1p-21, ub = ((double)a[2 * p + 1] + 0.5) * 0x1p-21;
             const double rad = sqrt(-2.0 * log(ua));
-            z[2 * p] = rad * cos(two_pi * ub);
-            z[2 * p + 1] = rad * sin(two_pi * ub);
+            double s, c;
+            sincospi(2.0 * ub, &s, &c);
+            z[2 * p] = rad * c;
+            z[2 * p + 1] = rad * s;
         }
     }
 };
@@ -135,6 +138,17 @@ __device__ __forceinline__ void len_inv(float r2, float &len, float &inv) {
 __device__ __forceinline__ void len_inv(double r2, double &len, double &inv) {
     len = sqrt(r2);
     inv = 1.0 / len;
+}
+
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// Orders a wavefront's LDS accesses before and after it (its lanes exchange data
+// through LDS without a workgroup barrier; the hardware keeps one wavefront's LDS
+// accesses in order, this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // ---------------------------------------------------------------------------

@@ -37,6 +37,7 @@ struct ProblemHost {
     std::vector<double> init;   // resolved shared start state x_o
     DevProblem dev{};
     int G = 1, B = 1;
+    int lanes_1d = 1;            // lanes per replica of the 1-D kernel
     int first_item = 0, n_items = 0;
     int item_windows = 1;        // most windows one work item's replicas fall in
     int64_t region_begin = 0, region_end = 0;   // byte range of this problem in the workspace
@@ -201,6 +202,26 @@ void default_shape(int N, int precision, int &G, int &B) {
     else { G = 64; B = 4; }
 }
 
+// Lanes per replica of the 1-D kernel for a number of replicas (all windows).
+// More lanes shorten a replica's own time (they share its noise and its
+// sampling exponentials) but every lane takes the steps, so they pay only while
+// SIMDs would idle: about one wavefront per SIMD (65536 lanes), half as many
+// again at four lanes.  MI355X, double well, 4000 steps, kernel ms in fp64 (fp32)
+// at 2 / 4 / 8 / 16 / 32 lanes:
+//   1344 replicas  0.90 / 0.53 / 0.35 / 0.29 / 0.23 (0.55 / 0.36 / 0.25 / 0.23 / 0.18)
+//   5376           0.90 / 0.54 / 0.36 / 0.40 / 0.48 (0.55 / 0.36 / 0.25 / 0.28 / 0.28)
+//   21504          0.90 / 0.80 / 0.80 / 1.20 / 1.58 (0.55 / 0.45 / 0.54 / 0.66 / 0.90)
+//   43008          1.34 / 1.22 / 1.47 / 2.03 / 2.81 (0.66 / 0.74 / 0.92 / 1.16 / 1.63)
+// and at 1 / 2 / 4 lanes (2000 steps): 86016 replicas 1.49 / 1.05 / 1.20 (0.49 /
+// 0.58 / 0.65), 688128: 8.00 / 6.22 / 7.22 (2.50 / 3.24 / 4.20).
+int default_lanes_1d(int64_t replicas, int precision) {
+    if (replicas <= 2048) return 32;
+    if (replicas <= 4096) return 16;
+    if (replicas <= 8192) return 8;
+    if (replicas <= 24576) return 4;
+    return precision == PPP_FP64 || replicas <= 65536 ? 2 : 1;
+}
+
 struct TuneEntry { int nmax, precision, G, B; };
 
 std::vector<TuneEntry> read_tune_table(const char *path) {
@@ -245,6 +266,8 @@ ppp_status build_problem(const ppp_problem *p, ProblemHost &ph, const std::vecto
     } else {
         ph.init.assign(1, p->init_coords ? p->init_coords[0] : p->lambda[0]);
         ph.G = 1; ph.B = 1;
+        const int64_t sim_windows = (p->flags & PPP_FLAG_SEQUENTIAL) ? 1 : (int64_t)p->n_windows + ((p->flags & PPP_FLAG_FREE_ENSEMBLE) ? 1 : 0);
+        ph.lanes_1d = default_lanes_1d(sim_windows * p->n_replicas, p->precision);
     }
     ph.p.init_coords = ph.init.data();
     DevProblem &d = ph.dev;
@@ -338,7 +361,7 @@ int64_t total_steps(const ProblemHost &ph) {
     return ph.dev.sequential ? (int64_t)ph.dev.n_windows * ph.dev.n_steps : ph.dev.n_steps;
 }
 
-int reps_per_item(const ProblemHost &ph) { return ph.dev.model == PPP_MODEL_CHAIN ? chain_reps_per_wg(ph.G) : WG; }
+int reps_per_item(const ProblemHost &ph) { return ph.dev.model == PPP_MODEL_CHAIN ? chain_reps_per_wg(ph.G) : WG / ph.lanes_1d; }
 
 // Work items of one problem.  Per window (every item inside one window), or,
 // for chain problems whose windows do not split into whole items, as runs of
@@ -435,8 +458,9 @@ ppp_status launch_items(ppp_handle *h, const ProblemHost &ph, int64_t b, int64_t
                         int64_t traj_rep, int first, int count) {
     const int64_t nk = (int64_t)ph.item_windows * ph.dev.xi_nbins;
     const int cap = nk <= kLdsHistCap ? (int)nk : 0;
+    const int G = ph.dev.model == PPP_MODEL_CHAIN ? ph.G : ph.lanes_1d;
     if (!ph.dev.sequential) {
-        HIPCHK(h, launch_sim(d_probs(h), d_items(h) + first, count, h->ws, b, e, ph.dev.model, ph.dev.precision, ph.G,
+        HIPCHK(h, launch_sim(d_probs(h), d_items(h) + first, count, h->ws, b, e, ph.dev.model, ph.dev.precision, G,
                              ph.B, traj, traj_rep, cap, st));
         return PPP_OK;
     }
@@ -447,7 +471,7 @@ ppp_status launch_items(ppp_handle *h, const ProblemHost &ph, int64_t b, int64_t
     do {
         const int64_t stop = std::min(e, (at / T + 1) * T);
         HIPCHK(h, launch_sim(d_probs(h), d_items(h) + first, count, h->ws, at, stop, ph.dev.model, ph.dev.precision,
-                             ph.G, ph.B, traj, traj_rep, cap, st));
+                             G, ph.B, traj, traj_rep, cap, st));
         at = stop;
     } while (at < e);
     return PPP_OK;

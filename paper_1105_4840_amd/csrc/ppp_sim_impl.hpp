@@ -7,7 +7,7 @@
 //   forward step and of the reverse step, each also for 2a (Kish size).
 //
 // Two kernels:
-//   * sim_1d: one lane per replica, overdamped dynamics of one coordinate.
+//   * sim_1d: L lanes per replica, overdamped dynamics of one coordinate.
 //   * sim_chain<T, G, B>: G consecutive lanes of a wavefront per replica (any G
 //     up to 64; 64 / G groups per wavefront, the remaining lanes idle), B beads
 //     per lane in registers (lane g owns beads gB .. gB+B-1).  The
@@ -159,7 +159,26 @@ template <typename T> __device__ __forceinline__ T *state_ptr(char *ws, const De
 // 1-D overdamped model: x_{n+1} = x_n + mu dt F(x_n) + sqrt(mu kT dt/2) (eta_n + eta_{n+1})
 // (Leimkuhler-Matthews) or + sqrt(2 mu kT dt) eta_{n+1} (Euler-Maruyama).
 // eta_n is component n mod 4 of the Philox block with counter (gid, n div 4, 0, 0).
+//
+// L consecutive lanes share a replica.  Bound: the instruction latency of one
+// wavefront (about 8 cycles an instruction while a SIMD holds one), not memory:
+// the double-well workload (21 windows x 256 replicas) fills 84 wavefronts at a
+// lane per replica, for 1024 SIMDs.  A replica's noise and its sampling
+// exponentials do not depend on the step in hand, so the lanes draw the normals
+// of a tile of 4LQ steps at once and pass them through LDS; all of them then take
+// the tile's steps (five dependent products each) from there, and afterwards
+// each evaluates the exponentials of one of the tile's samples.  Only the sums
+// that keep the samples' order are serial: one fused product per sample, each
+// sum on a lane of its own.  20000 steps of that workload in fp64: 12.3 ms at a
+// lane per replica, 1.8 ms here; 21 x 4096 replicas, 2000 steps: 1.8 and 1.05 ms.
 // ===========================================================================
+template <typename T, int POT>
+__device__ __forceinline__ T step_1d(T x, T c0, T b, T centre, T kr, T mu_dt, T amp, T e) {
+    // explicit fused products: the same rounding in the block loop and the edge loop
+    const T f = POT == 0 ? (c0 * x) * fma_t(x, x, -b) : c0 * x;
+    return fma_t(e, amp, fma_t(fma_t(-kr, x - centre, f), mu_dt, x));
+}
+
 template <typename T>
 __device__ __forceinline__ T force_1d(const DevProblem &P, T x, T centre, T kr) {
     T f;
@@ -171,11 +190,48 @@ __device__ __forceinline__ T force_1d(const DevProblem &P, T x, T centre, T kr) 
 // Restraint stiffness of window w: k, or 0 for the unrestrained ensemble (w = s).
 __device__ __forceinline__ double window_k(const DevProblem &P, int w) { return w < P.n_windows ? P.k : 0.0; }
 
-template <typename T>
-__device__ __forceinline__ void sim_1d_replica(const DevProblem &P, const WorkItem &item, int w, int rep, char *ws,
-                                               int64_t step_begin, int64_t step_end, double *traj, int traj_rep,
-                                               unsigned int *lhist) {
-    if ((int)threadIdx.x >= item.n_reps) return;
+// Lane l - OFF's value inside a row of 16 lanes (a DPP move: no trip through LDS).
+template <int OFF> __device__ __forceinline__ double row_shr(double v) {
+    I2 w = __builtin_bit_cast(I2, v);
+    w.lo = __builtin_amdgcn_update_dpp(w.lo, w.lo, 0x110 + OFF, 0xf, 0xf, false);
+    w.hi = __builtin_amdgcn_update_dpp(w.hi, w.hi, 0x110 + OFF, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, w);
+}
+
+// Running maximum of a over the group's lanes up to and including this one.
+template <int L> __device__ __forceinline__ double group_prefix_max(double a) {
+    const int l = (int)threadIdx.x & (L - 1);
+    double v = a;
+    if constexpr (L > 1) { const double o = row_shr<1>(v); v = l >= 1 ? fmax(v, o) : v; }
+    if constexpr (L > 2) { const double o = row_shr<2>(v); v = l >= 2 ? fmax(v, o) : v; }
+    if constexpr (L > 4) { const double o = row_shr<4>(v); v = l >= 4 ? fmax(v, o) : v; }
+    if constexpr (L > 8) { const double o = row_shr<8>(v); v = (l & 15) >= 8 ? fmax(v, o) : v; }
+    if constexpr (L > 16) { const double o = __shfl(v, 15, L); v = l >= 16 ? fmax(v, o) : v; }
+    return v;
+}
+
+// The sums of a record that depend on the order of the samples: S1, S2 and the
+// two log-sum-exp pairs.  Each takes a sample as S <- S alpha + beta; the
+// (alpha, beta) of a sample are found by its lane, and sum f is carried by lane
+// f mod L of the group.
+constexpr int kOrderedSums = 6;
+
+// LDS of one workgroup: the normals and positions of a tile (4Q steps per lane)
+// and the (alpha, beta) of up to L samples per group.  A group's normals start
+// 16 bytes further on than the last group's end, so the groups of a wavefront
+// read theirs from different banks.
+template <typename T, int L, int Q> struct Lds1d {
+    static constexpr int kZ = 4 * L * Q + 16 / (int)sizeof(T);
+    T z[(WG / L) * kZ + 4];      // a group reads up to four beyond its own
+    T x[(WG / L) * kZ];
+    double ab[kOrderedSums][WG][2];
+};
+
+template <typename T, int L, int Q, int POT>
+__device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int rep, char *ws, int64_t step_begin,
+                                               int64_t step_end, double *traj, int traj_rep, unsigned int *lhist,
+                                               Lds1d<T, L, Q> &lds) {
+    const int l = (int)threadIdx.x & (L - 1);
     // record (window, replica); the sequential protocol keeps one state per replica
     // and draws replica `rep`'s window-1 noise all the way
     const int64_t g = (int64_t)w * P.n_replicas + rep;
@@ -187,9 +243,10 @@ __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, const WorkIt
     unsigned long long *hist = reinterpret_cast<unsigned long long *>(ws + P.off_hist);
     T *st = state_ptr<T>(ws, P) + gs * 2;
     const double lam_w = lam[w];
-    const SampleCoef coef = sample_coef(P, lam, w);
+    const SampleCoef C = sample_coef(P, lam, w);
     const double x_start = reinterpret_cast<const double *>(ws + P.off_init)[0];
-    const int64_t n_end = step_end < s0 + P.n_steps ? step_end : s0 + P.n_steps;
+    // step numbers stay below 2^32 (the runtime checks n_steps, and n_windows n_steps when sequential)
+    const uint32_t n_end = (uint32_t)(step_end < s0 + P.n_steps ? step_end : s0 + P.n_steps);
 
     double acc[A_NFIELDS];
     T x, eta_prev;
@@ -209,50 +266,207 @@ __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, const WorkIt
         for (int f = 0; f < A_NFIELDS; ++f) acc[f] = acc_g[f];
         x = st[0]; eta_prev = st[1];
     }
-    const bool record = traj != nullptr && g == traj_rep;
+    const bool record = traj != nullptr && g == traj_rep && l == 0;
     if (record && step_begin == 0) traj[0] = (double)x;
     const T kr = (T)window_k(P, w);
     const T mu_dt = (T)(P.mobility * P.dt);
-    const T amp = P.integrator_1d == 0 ? (T)sqrt(0.5 * P.mobility * P.kT * P.dt)
-                                       : (T)sqrt(2.0 * P.mobility * P.kT * P.dt);
+    const bool lm = P.integrator_1d == 0;
+    const T amp = lm ? (T)sqrt(0.5 * P.mobility * P.kT * P.dt) : (T)sqrt(2.0 * P.mobility * P.kT * P.dt);
+    const T w_prev = lm ? (T)1 : (T)0;
+    const T c0 = POT == 0 ? (T)(-4.0 * P.pot_a) : (T)(-P.pot_kappa), pb = (T)P.pot_b;
+    const T c_fix = (T)lam_w;
     bool alive = acc[A_BLOWN] == 0.0;
-    T z[4];
-    uint32_t zblock = 0xFFFFFFFFu;
-    int64_t n_sample = s0 + next_sample_after(P, step_begin - s0);
-    for (int64_t n = step_begin + 1; n <= n_end && alive; ++n) {
-        const T F = force_1d<T>(P, x, (T)(w == 0 || !P.sequential ? centre_at(P, lam_w, n - 1) : lam_w), kr);
-        const uint32_t blk = (uint32_t)(n >> 2);
-        if (blk != zblock) { Normal4<T>::get(P.seed, gid, blk, 0u, 0u, z); zblock = blk; }
-        const T eta = z[n & 3];
-        if (P.integrator_1d == 0) x = x + mu_dt * F + amp * (eta_prev + eta);
-        else x = x + mu_dt * F + amp * eta;
-        eta_prev = eta;
-        if (record && n <= 100000) traj[n] = (double)x;
-        if (n == n_sample) {
-            n_sample += P.sample_every;
-            const double xi = (double)x;
-            if (!isfinite(xi) || fabs(xi) > P.xi_bound) { acc[A_BLOWN] = 1.0; alive = false; break; }
-            accumulate(P, coef, w, xi, acc, hist, lhist);
-        }
+    T x_dead = x, eta_dead = eta_prev;             // where a frozen replica stopped; its lanes run on unread
+    // the centre moves until step pull_end
+    const uint32_t pull_end = (P.n_pull > 0 && (w == 0 || !P.sequential)) ? (uint32_t)P.n_pull : 0u;
+
+    // fields read inside the loops, held in registers: the histogram's atomics keep
+    // the compiler from carrying loads of the record across them
+    const uint64_t seed = P.seed;
+    const double bound = P.xi_bound, xi_min = P.xi_min, xi_bin = P.xi_bin, k_bins = (double)P.xi_nbins;
+    const uint32_t every = (uint32_t)P.sample_every;
+    unsigned long long *hist_w = hist + (int64_t)w * P.xi_nbins;
+
+    // the forward and reverse exponents of a sample: c (e - h) or c e e with e = xi - ref
+    const double ref_f = C.kind_f == 1 ? lam_w : C.ref_f, cf = C.kind_f == 1 ? C.cf : C.qf;
+    const double ref_r = C.kind_r == 1 ? lam_w : C.ref_r, cr = C.kind_r == 1 ? C.cr : C.qr;
+
+    const int t0 = (int)threadIdx.x & ~(L - 1), lane0 = lane_id() & ~(L - 1);
+    const uint64_t group_mask = ((1ull << L) - 1) << lane0;
+    T *zg = lds.z + ((int)threadIdx.x / L) * Lds1d<T, L, Q>::kZ;
+    T *xg = lds.x + ((int)threadIdx.x / L) * Lds1d<T, L, Q>::kZ;
+    constexpr uint32_t kTile = 4u * L * Q;         // steps whose normals are drawn together
+    // offset of lane l's sample from the first one of a tile (beyond any tile if it cannot lie in the first one's)
+    const uint32_t lane_off = l == 0 ? 0u : (every < kTile ? (uint32_t)l * every : 0x40000000u);
+    double x_min = acc[A_XMIN], x_max = acc[A_XMAX];
+    constexpr int kSumField[kOrderedSums] = {A_S1, A_S2, A_SF, A_SF2, A_SR, A_SR2};
+    constexpr int kOwn = (kOrderedSums + L - 1) / L;   // sums carried by one lane
+    double own[kOwn];
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+        own[i] = 0.0;
+#pragma unroll
+        for (int f = 0; f < kOrderedSums; ++f) own[i] = f == i * L + l ? acc[kSumField[f]] : own[i];
     }
-    for (int f = 0; f < A_NFIELDS; ++f) acc_g[f] = acc[f];
-    st[0] = x; st[1] = eta_prev;
+
+    uint32_t n = (uint32_t)step_begin;
+    uint32_t n_sample = (uint32_t)(s0 + next_sample_after(P, step_begin - s0));
+    while (n < n_end && __any(alive)) {
+        // a tile: kTile steps from `base`; their normals, Q Philox blocks per lane
+        const uint32_t base = (n + 1) & ~(kTile - 1u);
+#pragma unroll 1
+        for (int c = 0; c < Q; ++c) {
+            T z[4];
+            Normal4<T>::get(seed, gid, (base >> 2) + (uint32_t)(c * L + l), 0u, 0u, z);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) zg[4 * (c * L + l) + q] = z[q];
+        }
+        wave_lds_sync();
+        const uint32_t last = base + kTile - 1u, stop = last < n_end ? last : n_end;
+        const int hi = (int)(stop - base);
+        int k = (int)(n + 1 - base);
+        // whole blocks of four steps with the centre at rest, up to here
+        const int fast_end = (n + 1 > pull_end && !traj) ? (hi + 1) & ~3 : 0;
+        while (k <= hi) {
+            if ((k & 3) == 0 && k < fast_end) {
+                T e[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) e[q] = zg[k + q];
+#pragma unroll 2
+                for (; k < fast_end; k += 4) {
+                    T en[4], xq[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) en[q] = zg[k + 4 + q];   // past the last block: unread
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        x = step_1d<T, POT>(x, c0, pb, c_fix, kr, mu_dt, amp, fma_t(w_prev, eta_prev, e[q]));
+                        eta_prev = e[q];
+                        xq[q] = x;
+                        e[q] = en[q];
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) xg[k + q] = xq[q];
+                }
+            } else {
+                const uint32_t step = base + (uint32_t)k;
+                const T eta = zg[k];
+                const T c = pull_end > 0 ? (T)centre_at(P, lam_w, (int64_t)step - 1) : c_fix;
+                x = step_1d<T, POT>(x, c0, pb, c, kr, mu_dt, amp, fma_t(w_prev, eta_prev, eta));
+                eta_prev = eta;
+                xg[k] = x;
+                if (record && alive && step <= 100000u) traj[step] = (double)x;
+                ++k;
+            }
+        }
+        wave_lds_sync();
+        // the tile's samples, one per lane (in passes of L where there are more)
+        for (uint32_t so = n_sample - base; so <= (uint32_t)hi;) {
+            const uint32_t o = so + lane_off;
+            const bool in = o <= (uint32_t)hi;
+            const int cnt = (int)__popcll(__ballot(in) & group_mask);
+            const double xi = in ? (double)xg[o] : 0.0;
+            bool mine = in && alive;
+            const uint64_t bad = __ballot(mine && (!isfinite(xi) || fabs(xi) > bound)) & group_mask;
+            if (bad) {
+                // frozen at its first bad sample: later ones are dropped, its state stays there
+                const int first = __ffsll((unsigned long long)(bad >> lane0)) - 1;
+                const uint32_t of = so + (first ? (uint32_t)first * every : 0u);
+                x_dead = xg[of]; eta_dead = zg[of];
+                acc[A_BLOWN] = 1.0;
+                alive = false;
+                mine = mine && l < first;
+            }
+            const double d = mine ? xi - lam_w : 0.0;
+            const double ef = xi - ref_f, er = xi - ref_r;
+            const double af = mine && C.kind_f ? (C.kind_f == 1 ? cf * (ef - C.hf) : cf * ef * ef) : -INFINITY;
+            const double ar = mine && C.kind_r ? (C.kind_r == 1 ? cr * (er - C.hr) : cr * er * er) : -INFINITY;
+            const double pf = group_prefix_max<L>(af), pr = group_prefix_max<L>(ar);
+            // the maximum before this sample
+            double mf = row_shr<1>(pf), mr = row_shr<1>(pr);
+            if constexpr (L > 16) {
+                const double bf = __shfl(pf, 15, L), br = __shfl(pr, 15, L);
+                mf = l == 16 ? bf : mf; mr = l == 16 ? br : mr;
+            }
+            mf = l > 0 ? fmax(acc[A_MF], mf) : acc[A_MF];
+            mr = l > 0 ? fmax(acc[A_MR], mr) : acc[A_MR];
+            acc[A_MF] = fmax(acc[A_MF], __shfl(pf, L - 1, L));
+            acc[A_MR] = fmax(acc[A_MR], __shfl(pr, L - 1, L));
+            const double df = af - mf, dr = ar - mr;
+            const bool uf = df > 0.0, ur = dr > 0.0;
+            // no sample, or no step in this direction: alpha = 1, beta = 0
+            const double tf = mine && C.kind_f ? exp(-fabs(df)) : 0.0, tr = mine && C.kind_r ? exp(-fabs(dr)) : 0.0;
+            const double tf2 = tf * tf, tr2 = tr * tr;
+            const double ab[kOrderedSums][2] = {{1.0, d}, {1.0, d * d},
+                                                {uf ? tf : 1.0, uf ? 1.0 : tf}, {uf ? tf2 : 1.0, uf ? 1.0 : tf2},
+                                                {ur ? tr : 1.0, ur ? 1.0 : tr}, {ur ? tr2 : 1.0, ur ? 1.0 : tr2}};
+#pragma unroll
+            for (int f = 0; f < kOrderedSums; ++f) { lds.ab[f][threadIdx.x][0] = ab[f][0]; lds.ab[f][threadIdx.x][1] = ab[f][1]; }
+            bool under = false, over = false;
+            if (mine) {
+                x_min = fmin(x_min, xi);
+                x_max = fmax(x_max, xi);
+                const double fb = floor((xi - xi_min) / xi_bin);
+                if (fb < 0.0) under = true;
+                else if (fb >= k_bins) over = true;
+                else if (lhist) atomicAdd(lhist + (int)fb, 1u);
+                else atomicAdd(hist_w + (int64_t)fb, 1ull);
+            }
+            acc[A_N] += (double)__popcll(__ballot(mine) & group_mask);
+            acc[A_UNDER] += (double)__popcll(__ballot(under) & group_mask);
+            acc[A_OVER] += (double)__popcll(__ballot(over) & group_mask);
+            wave_lds_sync();
+            // in sample order, so the sums do not depend on how the run is cut into launches
+#pragma unroll
+            for (int i = 0; i < kOwn; ++i) {
+                const int f = i * L + l < kOrderedSums ? i * L + l : kOrderedSums - 1;
+                const double *ab_f = &lds.ab[f][t0][0];
+#pragma unroll 4
+                for (int j = 0; j < cnt; ++j) own[i] = fma(own[i], ab_f[2 * j], ab_f[2 * j + 1]);
+            }
+            wave_lds_sync();
+            so += (uint32_t)cnt * every;
+            n_sample += (uint32_t)cnt * every;
+        }
+        n = stop;
+    }
+#pragma unroll
+    for (int off = 1; off < L; off <<= 1) {
+        x_min = fmin(x_min, __shfl_xor(x_min, off, L));
+        x_max = fmax(x_max, __shfl_xor(x_max, off, L));
+    }
+    acc[A_MF2] = 2.0 * acc[A_MF]; acc[A_MR2] = 2.0 * acc[A_MR];
+    acc[A_XMIN] = x_min; acc[A_XMAX] = x_max;
+    if (l == 0) {
+        for (int f = 0; f < A_NFIELDS; ++f)
+            if (f != A_S1 && f != A_S2 && f != A_SF && f != A_SF2 && f != A_SR && f != A_SR2) acc_g[f] = acc[f];
+        st[0] = alive ? x : x_dead; st[1] = alive ? eta_prev : eta_dead;
+    }
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i)
+        if (i * L + l < kOrderedSums) {
+            const int f = i * L + l;
+            acc_g[f < 2 ? A_S1 + f : (f < 4 ? (f == 2 ? A_SF : A_SF2) : (f == 4 ? A_SR : A_SR2))] = own[i];
+        }
 }
 
-template <typename T>
+template <typename T, int L, int Q>
 __global__ __launch_bounds__(WG) void sim_1d(const DevProblem *__restrict__ probs, const WorkItem *__restrict__ items,
                                              int n_items, char *__restrict__ ws, int64_t step_begin,
                                              int64_t step_end, double *__restrict__ traj, int traj_rep, int lds_cap) {
     extern __shared__ unsigned int s_hist[];
+    __shared__ Lds1d<T, L, Q> lds;
     const int it = blockIdx.x;
     if (it >= n_items) return;
     const WorkItem item = items[it];
     const DevProblem &P = probs[item.prob];
     const int w = P.sequential ? (int)seq_window(P, step_begin) : item.window;
-    const int rep = item.rep_begin + (int)threadIdx.x;
+    const int r = (int)threadIdx.x / L;
     unsigned int *lhist = P.xi_nbins <= lds_cap ? s_hist : nullptr;
     if (lhist) lhist_clear(lhist, P.xi_nbins);
-    sim_1d_replica<T>(P, item, w, rep, ws, step_begin, step_end, traj, traj_rep, lhist);
+    if (r < item.n_reps) {
+        if (P.pot_kind == 0) sim_1d_replica<T, L, Q, 0>(P, w, item.rep_begin + r, ws, step_begin, step_end, traj, traj_rep, lhist, lds);
+        else sim_1d_replica<T, L, Q, 1>(P, w, item.rep_begin + r, ws, step_begin, step_end, traj, traj_rep, lhist, lds);
+    }
     if (lhist) lhist_flush(lhist, P.xi_nbins, reinterpret_cast<unsigned long long *>(ws + P.off_hist) + (int64_t)w * P.xi_nbins);
 }
 
