@@ -39,6 +39,71 @@ __device__ __forceinline__ float unit_f32(uint32_t r) {
     return __uint_as_float(__builtin_amdgcn_alignbit(0x7fu, r, 9u)) - 0.99999994039535522f;
 }
 
+// ---------------------------------------------------------------------------
+// Box-Muller in fp64 on u = f 2^-BITS, f = integer + 1/2 below 2^BITS (exact).
+// The three functions it needs take arguments of one narrow kind here, so each
+// is a short polynomial without a library function's range checks: a block's two
+// pairs and its Philox words take 215 vector instructions, 359 with the
+// library's log, sqrt and sincospi, and the noise is half of the fp64 1-D
+// kernel's instructions.  Largest errors over 2e7 arguments, edges included, in
+// units of 2^-53 (relative; absolute for cos and sin): -2 ln u 2.0, sqrt 1.0,
+// cos and sin 1.8; the library's cos of the rounded product 2 pi u has 5.8.
+// ---------------------------------------------------------------------------
+
+// -2 ln u.  f = 2^k m with m in [sqrt(1/2), sqrt 2), ln m = 2 atanh s with s =
+// (m - 1) / (m + 1), |s| <= 0.1716, by the series of atanh to s^19 (the next
+// term is 2.3e-17 of the first).
+template <int BITS> __device__ __forceinline__ double minus_2_ln(double f) {
+    const uint64_t w = __builtin_bit_cast(uint64_t, f);
+    constexpr uint32_t kHalfSqrt = 0x3fe6a09eu;             // upper word of sqrt(1/2)
+    const uint32_t t = (uint32_t)(w >> 32) - kHalfSqrt;
+    const int k = (int)t >> 20;
+    const uint32_t mh = (t & 0xfffffu) + kHalfSqrt;
+    const double m = __builtin_bit_cast(double, ((uint64_t)mh << 32) | (uint32_t)w);
+    const double num = m - 1.0, den = m + 1.0;
+    const double r0 = (double)__builtin_amdgcn_rcpf((float)den);
+    const double r = __builtin_fma(r0, __builtin_fma(-den, r0, 1.0), r0);
+    const double s0 = num * r;
+    const double s = __builtin_fma(__builtin_fma(-den, s0, num), r, s0);
+    const double q = s * s;
+    const double p = q * __builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(0.05263157894736842, q, 0.058823529411764705), q, 0.06666666666666667), q, 0.07692307692307693), q, 0.09090909090909091), q, 0.1111111111111111), q, 0.14285714285714285), q, 0.2), q, 0.3333333333333333);
+    return __builtin_fma((double)(k - BITS), -1.3862943611198906, -4.0 * __builtin_fma(s, p, s));
+}
+
+// sqrt of a positive number of ordinary size: two Newton steps from the fp32
+// reciprocal square root, the second on the residual.
+__device__ __forceinline__ double sqrt_positive(double x) {
+    const double y = (double)__builtin_amdgcn_rsqf((float)x);
+    const double g = x * y, h = 0.5 * y;
+    const double e = __builtin_fma(-h, g, 0.5);
+    const double g1 = __builtin_fma(g, e, g), h1 = __builtin_fma(h, e, h);
+    return __builtin_fma(__builtin_fma(-g1, g1, x), h1, g1);
+}
+
+// cos and sin of 2 pi u: u is an odd multiple of a power of two, so its distance
+// p (in quarter turns) from the nearest multiple of a quarter is exact; Taylor
+// series of sin and cos of p pi/2, |p| <= 1/2, to p^15 and p^16.
+template <int BITS> __device__ __forceinline__ void turn_cos_sin(double f, double &c, double &s) {
+    constexpr double kScale = 4.0 / (double)(1ull << BITS);
+    const double t = f * kScale;
+    const double qd = __builtin_rint(t);
+    const double p = t - qd, p2 = p * p;
+    const uint32_t q = (uint32_t)(int)qd;
+    const double ss = __builtin_fma(p * p2, __builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(-6.688035109811468e-10, p2, 5.692172921967927e-08), p2, -3.598843235212085e-06), p2, 0.00016044118478735983), p2, -0.004681754135318688), p2, 0.07969262624616705), p2, -0.6459640975062463), p * 1.5707963267948966);
+    const double cc = __builtin_fma(p2, __builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(__builtin_fma(6.565963114979473e-11, p2, -6.386603083791852e-09), p2, 4.710874778818172e-07), p2, -2.5202042373060607e-05), p2, 0.0009192602748394266), p2, -0.02086348076335296), p2, 0.25366950790104803), p2, -1.2337005501361697), 1.0);
+    const double a = (q & 1u) ? ss : cc, b = (q & 1u) ? cc : ss;
+    c = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, a) ^ ((uint64_t)((q + 1u) & 2u) << 62));
+    s = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, b) ^ ((uint64_t)(q & 2u) << 62));
+}
+
+template <int BITS> __device__ __forceinline__ void box_muller(double fa, double fb, double &z0, double &z1) {
+    const double rad = sqrt_positive(minus_2_ln<BITS>(fa));
+    double c, s;
+    turn_cos_sin<BITS>(fb, c, s);
+    z0 = rad * c;
+    z1 = rad * s;
+}
+
 // Four standard normals per Philox block by Box-Muller, in the requested
 // precision.  fp64: u = (r + 1/2) 2^-32 (exact); fp32: u = (r>>9 + 1/2) 2^-23
 // (exact in fp32, hardware log2/sqrt/sin/cos; sin and cos take turns).
@@ -47,16 +112,9 @@ template <typename T> struct Normal4;
 template <> struct Normal4<double> {
     __device__ __forceinline__ static void get(uint64_t seed, uint32_t c0, uint32_t c1, uint32_t c2,
                                                uint32_t c3, double z[4]) {
-        U4 r = philox(seed, c0, c1, c2, c3);
-        const double scale = 1.0 / 4294967296.0;
-        double ua = ((double)r.x + 0.5) * scale, ub = ((double)r.y + 0.5) * scale;
-        double uc = ((double)r.z + 0.5) * scale, ud = ((double)r.w + 0.5) * scale;
-        double ra = sqrt(-2.0 * log(ua)), rc = sqrt(-2.0 * log(uc));
-        double sb, cb, sd, cd;
-        sincospi(2.0 * ub, &sb, &cb);
-        sincospi(2.0 * ud, &sd, &cd);
-        z[0] = ra * cb; z[1] = ra * sb;
-        z[2] = rc * cd; z[3] = rc * sd;
+        const U4 r = philox(seed, c0, c1, c2, c3);
+        box_muller<32>((double)r.x + 0.5, (double)r.y + 0.5, z[0], z[1]);
+        box_muller<32>((double)r.z + 0.5, (double)r.w + 0.5, z[2], z[3]);
     }
 };
 
@@ -89,14 +147,7 @@ template <> struct Normal6<double> {
         const uint32_t a[6] = {r.x >> 11, r.y >> 11, r.z >> 11, r.w >> 11, ((r.x & 0x7ffu) << 10) | (r.y & 0x3ffu),
                                ((r.z & 0x7ffu) << 10) | (r.w & 0x3ffu)};
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            const double ua = ((double)a[2 * p] + 0.5) * 0x1p-21, ub = ((double)a[2 * p + 1] + 0.5) * 0x1p-21;
-            const double rad = sqrt(-2.0 * log(ua));
-            double s, c;
-            sincospi(2.0 * ub, &s, &c);
-            z[2 * p] = rad * c;
-            z[2 * p + 1] = rad * s;
-        }
+        for (int p = 0; p < 3; ++p) box_muller<21>((double)a[2 * p] + 0.5, (double)a[2 * p + 1] + 0.5, z[2 * p], z[2 * p + 1]);
     }
 };
 
@@ -142,14 +193,6 @@ __device__ __forceinline__ void len_inv(double r2, double &len, double &inv) {
 
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
-// Orders a wavefront's LDS accesses before and after it (its lanes exchange data
-// through LDS without a workgroup barrier; the hardware keeps one wavefront's LDS
-// accesses in order, this keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 // ---------------------------------------------------------------------------
 // Running log-sum-exp (m, S): ln sum_k exp(a_k) = m + ln S.

@@ -205,21 +205,20 @@ void default_shape(int N, int precision, int &G, int &B) {
 // Lanes per replica of the 1-D kernel for a number of replicas (all windows).
 // More lanes shorten a replica's own time (they share its noise and its
 // sampling exponentials) but every lane takes the steps, so they pay only while
-// SIMDs would idle: about one wavefront per SIMD (65536 lanes), half as many
-// again at four lanes.  MI355X, double well, 4000 steps, kernel ms in fp64 (fp32)
-// at 2 / 4 / 8 / 16 / 32 lanes:
-//   1344 replicas  0.90 / 0.53 / 0.35 / 0.29 / 0.23 (0.55 / 0.36 / 0.25 / 0.23 / 0.18)
-//   5376           0.90 / 0.54 / 0.36 / 0.40 / 0.48 (0.55 / 0.36 / 0.25 / 0.28 / 0.28)
-//   21504          0.90 / 0.80 / 0.80 / 1.20 / 1.58 (0.55 / 0.45 / 0.54 / 0.66 / 0.90)
-//   43008          1.34 / 1.22 / 1.47 / 2.03 / 2.81 (0.66 / 0.74 / 0.92 / 1.16 / 1.63)
-// and at 1 / 2 / 4 lanes (2000 steps): 86016 replicas 1.49 / 1.05 / 1.20 (0.49 /
-// 0.58 / 0.65), 688128: 8.00 / 6.22 / 7.22 (2.50 / 3.24 / 4.20).
-int default_lanes_1d(int64_t replicas, int precision) {
-    if (replicas <= 2048) return 32;
+// SIMDs would idle: up to one wavefront per SIMD (65536 lanes), twice or three
+// times that where the next split is the coarse one.  MI355X, double well, 2000
+// steps, kernel ms in fp64 (fp32) at 1 / 2 / 4 / 8 / 16 lanes:
+//   2688 replicas  0.56 / 0.34 / 0.22 / 0.16 / 0.12 (0.35 / 0.22 / 0.16 / 0.12 / 0.09)
+//   5376           0.57 / 0.34 / 0.22 / 0.17 / 0.18 (0.35 / 0.22 / 0.16 / 0.12 / 0.13)
+//   8400           0.56 / 0.40 / 0.22 / 0.24 / 0.25 (0.35 / 0.24 / 0.16 / 0.16 / 0.19)
+//   43008          0.56 / 0.49 / 0.44 / 0.58 / 0.81 (0.35 / 0.28 / 0.27 / 0.38 / 0.58)
+//   86016          0.81 / 0.67 / 0.81 / 1.03 / 1.48 (0.43 / 0.36 / 0.48 / 0.68 / 1.06)
+//   172032         1.10 / 1.21 / 1.37 / 1.85 / 2.89 (0.53 / 0.66 / 0.83 / 1.24 / 2.08)
+int default_lanes_1d(int64_t replicas) {
     if (replicas <= 4096) return 16;
     if (replicas <= 8192) return 8;
-    if (replicas <= 24576) return 4;
-    return precision == PPP_FP64 || replicas <= 65536 ? 2 : 1;
+    if (replicas <= 49152) return 4;
+    return replicas <= 131072 ? 2 : 1;
 }
 
 struct TuneEntry { int nmax, precision, G, B; };
@@ -267,7 +266,7 @@ ppp_status build_problem(const ppp_problem *p, ProblemHost &ph, const std::vecto
         ph.init.assign(1, p->init_coords ? p->init_coords[0] : p->lambda[0]);
         ph.G = 1; ph.B = 1;
         const int64_t sim_windows = (p->flags & PPP_FLAG_SEQUENTIAL) ? 1 : (int64_t)p->n_windows + ((p->flags & PPP_FLAG_FREE_ENSEMBLE) ? 1 : 0);
-        ph.lanes_1d = default_lanes_1d(sim_windows * p->n_replicas, p->precision);
+        ph.lanes_1d = default_lanes_1d(sim_windows * p->n_replicas);
     }
     ph.p.init_coords = ph.init.data();
     DevProblem &d = ph.dev;

@@ -24,6 +24,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "ppp_device.hpp"
 #include "ppp_launch.hpp"
 #include "ppp_chain_force.hpp"
@@ -161,17 +163,28 @@ template <typename T> __device__ __forceinline__ T *state_ptr(char *ws, const De
 // eta_n is component n mod 4 of the Philox block with counter (gid, n div 4, 0, 0).
 //
 // L consecutive lanes share a replica.  Bound: the instruction latency of one
-// wavefront (about 8 cycles an instruction while a SIMD holds one), not memory:
+// wavefront (4 to 6 cycles an instruction while a SIMD holds one), not memory:
 // the double-well workload (21 windows x 256 replicas) fills 84 wavefronts at a
 // lane per replica, for 1024 SIMDs.  A replica's noise and its sampling
 // exponentials do not depend on the step in hand, so the lanes draw the normals
-// of a tile of 4LQ steps at once and pass them through LDS; all of them then take
-// the tile's steps (five dependent products each) from there, and afterwards
-// each evaluates the exponentials of one of the tile's samples.  Only the sums
-// that keep the samples' order are serial: one fused product per sample, each
-// sum on a lane of its own.  20000 steps of that workload in fp64: 12.3 ms at a
-// lane per replica, 1.8 ms here; 21 x 4096 replicas, 2000 steps: 1.8 and 1.05 ms.
+// of a tile of 4L steps at once, one Philox block each, and all of them take the
+// tile's steps (five dependent products each), each block's normals broadcast
+// from its lane by DPP moves: through LDS they cost a third more, its reads being
+// shared by the CU's wavefronts.  Pending samples wait in a lane each until the
+// next tile's might not fit, and are then folded together, every lane evaluating
+// its sample's exponentials.  Only the sums that keep the samples' order are
+// serial: one fused product per sample, each sum on a lane of its own.  20000
+// steps of that workload in fp64: 12.3 ms at a lane per replica, 1.7 ms here;
+// 21 x 4096 replicas, 2000 steps: 1.75 and 0.67 ms.
 // ===========================================================================
+// Orders a wavefront's LDS accesses before and after it (its lanes exchange data
+// through LDS without a workgroup barrier; the hardware keeps one wavefront's LDS
+// accesses in order, this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 template <typename T, int POT>
 __device__ __forceinline__ T step_1d(T x, T c0, T b, T centre, T kr, T mu_dt, T amp, T e) {
     // explicit fused products: the same rounding in the block loop and the edge loop
@@ -205,8 +218,7 @@ template <int L> __device__ __forceinline__ double group_prefix_max(double a) {
     if constexpr (L > 1) { const double o = row_shr<1>(v); v = l >= 1 ? fmax(v, o) : v; }
     if constexpr (L > 2) { const double o = row_shr<2>(v); v = l >= 2 ? fmax(v, o) : v; }
     if constexpr (L > 4) { const double o = row_shr<4>(v); v = l >= 4 ? fmax(v, o) : v; }
-    if constexpr (L > 8) { const double o = row_shr<8>(v); v = (l & 15) >= 8 ? fmax(v, o) : v; }
-    if constexpr (L > 16) { const double o = __shfl(v, 15, L); v = l >= 16 ? fmax(v, o) : v; }
+    if constexpr (L > 8) { const double o = row_shr<8>(v); v = l >= 8 ? fmax(v, o) : v; }
     return v;
 }
 
@@ -216,21 +228,45 @@ template <int L> __device__ __forceinline__ double group_prefix_max(double a) {
 // f mod L of the group.
 constexpr int kOrderedSums = 6;
 
-// LDS of one workgroup: the normals and positions of a tile (4Q steps per lane)
-// and the (alpha, beta) of up to L samples per group.  A group's normals start
-// 16 bytes further on than the last group's end, so the groups of a wavefront
-// read theirs from different banks.
-template <typename T, int L, int Q> struct Lds1d {
-    static constexpr int kZ = 4 * L * Q + 16 / (int)sizeof(T);
-    T z[(WG / L) * kZ + 4];      // a group reads up to four beyond its own
-    T x[(WG / L) * kZ];
-    double ab[kOrderedSums][WG][2];
+// LDS of one workgroup: the (alpha, beta) of up to L samples per group.  Seven
+// places of 16 bytes a lane for the six pairs, and six more between groups of 16
+// lanes, so that the lanes of a wavefront that read one sample's pairs for their
+// groups reach different banks.
+struct Lds1d {
+    double2 ab[WG * 7 + (WG / 16) * 6];
 };
+template <int L> __device__ __forceinline__ int ab_place(int thread) { return thread * 7 + (L == 16 ? (thread >> 4) * 6 : 0); }
 
-template <typename T, int L, int Q, int POT>
+// Lane B's value of the group, in every lane of it (DPP moves: no trip through LDS).
+template <int L, int B> __device__ __forceinline__ int group_bcast(int v) {
+    if constexpr (L == 16) return __builtin_amdgcn_update_dpp(v, v, 0x150 + B, 0xf, 0xf, false);
+    else if constexpr (L == 8) {      // two groups a row of 16: lanes 0-7, then 8-15
+        const int lo = __builtin_amdgcn_update_dpp(v, v, 0x150 + B, 0xf, 0x3, false);
+        return __builtin_amdgcn_update_dpp(lo, v, 0x150 + 8 + B, 0xf, 0xc, false);
+    }
+    else if constexpr (L == 4) return __builtin_amdgcn_update_dpp(v, v, B * 0x55, 0xf, 0xf, false);
+    else if constexpr (L == 2) return __builtin_amdgcn_update_dpp(v, v, B * 0x55 + 0xa0, 0xf, 0xf, false);
+    else return v;
+}
+template <int L, int B> __device__ __forceinline__ float group_bcast(float v) {
+    return __int_as_float(group_bcast<L, B>(__float_as_int(v)));
+}
+template <int L, int B> __device__ __forceinline__ double group_bcast(double v) {
+    const I2 w = __builtin_bit_cast(I2, v);
+    return __builtin_bit_cast(double, I2{group_bcast<L, B>(w.lo), group_bcast<L, B>(w.hi)});
+}
+
+template <int N, typename Fn> __device__ __forceinline__ void static_for(Fn &&fn) {
+    if constexpr (N > 0) {
+        static_for<N - 1>(fn);
+        fn(std::integral_constant<int, N - 1>{});
+    }
+}
+
+template <typename T, int L, int POT>
 __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int rep, char *ws, int64_t step_begin,
                                                int64_t step_end, double *traj, int traj_rep, unsigned int *lhist,
-                                               Lds1d<T, L, Q> &lds) {
+                                               Lds1d &lds) {
     const int l = (int)threadIdx.x & (L - 1);
     // record (window, replica); the sequential protocol keeps one state per replica
     // and draws replica `rep`'s window-1 noise all the way
@@ -293,11 +329,11 @@ __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int r
 
     const int t0 = (int)threadIdx.x & ~(L - 1), lane0 = lane_id() & ~(L - 1);
     const uint64_t group_mask = ((1ull << L) - 1) << lane0;
-    T *zg = lds.z + ((int)threadIdx.x / L) * Lds1d<T, L, Q>::kZ;
-    T *xg = lds.x + ((int)threadIdx.x / L) * Lds1d<T, L, Q>::kZ;
-    constexpr uint32_t kTile = 4u * L * Q;         // steps whose normals are drawn together
-    // offset of lane l's sample from the first one of a tile (beyond any tile if it cannot lie in the first one's)
-    const uint32_t lane_off = l == 0 ? 0u : (every < kTile ? (uint32_t)l * every : 0x40000000u);
+    constexpr uint32_t kTile = 4u * L;             // steps whose normals are drawn together
+    const int per_tile = every < kTile ? (int)((kTile - 1u) / every) + 1 : 1;   // most samples in a tile
+    int cnt = 0;                                   // pending samples, the j-th in lane j of the group
+    T xs[4] = {0, 0, 0, 0}, es[4] = {0, 0, 0, 0};  // this lane's: xs[qs], and es[qs] the normal of its step
+    int qs = 0;
     double x_min = acc[A_XMIN], x_max = acc[A_XMAX];
     constexpr int kSumField[kOrderedSums] = {A_S1, A_S2, A_SF, A_SF2, A_SR, A_SR2};
     constexpr int kOwn = (kOrderedSums + L - 1) / L;   // sums carried by one lane
@@ -309,125 +345,132 @@ __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int r
         for (int f = 0; f < kOrderedSums; ++f) own[i] = f == i * L + l ? acc[kSumField[f]] : own[i];
     }
 
-    uint32_t n = (uint32_t)step_begin;
+    uint32_t n = (uint32_t)step_begin, drawn = 1u;   // drawn: the tile z belongs to (tiles start at multiples of 4)
     uint32_t n_sample = (uint32_t)(s0 + next_sample_after(P, step_begin - s0));
+    T z[4];
     while (n < n_end && __any(alive)) {
-        // a tile: kTile steps from `base`; their normals, Q Philox blocks per lane
-        const uint32_t base = (n + 1) & ~(kTile - 1u);
-#pragma unroll 1
-        for (int c = 0; c < Q; ++c) {
-            T z[4];
-            Normal4<T>::get(seed, gid, (base >> 2) + (uint32_t)(c * L + l), 0u, 0u, z);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) zg[4 * (c * L + l) + q] = z[q];
+        // the tile of step n + 1: kTile steps from `base`, block b of four steps with its normals in lane b
+        const uint32_t base = (n + 1) & ~(kTile - 1u), last = base + kTile - 1u;
+        if (base != drawn) {
+            Normal4<T>::get(seed, gid, (base >> 2) + (uint32_t)l, 0u, 0u, z);
+            drawn = base;
         }
-        wave_lds_sync();
-        const uint32_t last = base + kTile - 1u, stop = last < n_end ? last : n_end;
-        const int hi = (int)(stop - base);
-        int k = (int)(n + 1 - base);
-        // whole blocks of four steps with the centre at rest, up to here
-        const int fast_end = (n + 1 > pull_end && !traj) ? (hi + 1) & ~3 : 0;
-        while (k <= hi) {
-            if ((k & 3) == 0 && k < fast_end) {
-                T e[4];
+        const uint32_t first = n + 1 - base;
+        if ((first == 0 || n == 0) && last <= n_end && n >= pull_end && every >= 4u && !traj) {
+            // a whole tile (its step 0, at the very start, is none) with the centre at
+            // rest and at most one sample in four steps
+            static_for<L>([&](auto bi) {
+                constexpr int b = bi.value;
+                T e[4], xq[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) e[q] = zg[k + q];
-#pragma unroll 2
-                for (; k < fast_end; k += 4) {
-                    T en[4], xq[4];
+                for (int q = 0; q < 4; ++q) e[q] = group_bcast<L, b>(z[q]);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) en[q] = zg[k + 4 + q];   // past the last block: unread
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
+                for (int q = 0; q < 4; ++q) {
+                    if (b > 0 || q > 0 || first == 0)
                         x = step_1d<T, POT>(x, c0, pb, c_fix, kr, mu_dt, amp, fma_t(w_prev, eta_prev, e[q]));
-                        eta_prev = e[q];
-                        xq[q] = x;
-                        e[q] = en[q];
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) xg[k + q] = xq[q];
+                    eta_prev = e[q];
+                    xq[q] = x;
                 }
-            } else {
-                const uint32_t step = base + (uint32_t)k;
-                const T eta = zg[k];
-                const T c = pull_end > 0 ? (T)centre_at(P, lam_w, (int64_t)step - 1) : c_fix;
-                x = step_1d<T, POT>(x, c0, pb, c, kr, mu_dt, amp, fma_t(w_prev, eta_prev, eta));
+                const uint32_t q = n_sample - (base + 4u * b);
+                if (q < 4u) {
+                    // the block's four positions; the fold picks the sampled one
+                    if (l == cnt) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) { xs[i] = xq[i]; es[i] = e[i]; }
+                        qs = (int)q;
+                    }
+                    n_sample += every;
+                    ++cnt;
+                }
+            });
+            n = last;
+        } else {
+            const uint32_t stop = last < n_end ? last : n_end;
+            do {
+                const uint32_t k = ++n - base;
+                T eta = z[0];
+#pragma unroll
+                for (int q = 1; q < 4; ++q) eta = (k & 3u) == (uint32_t)q ? z[q] : eta;
+                eta = __shfl(eta, (int)(k >> 2), L);
+                const T cen = pull_end > 0 ? (T)centre_at(P, lam_w, (int64_t)n - 1) : c_fix;
+                x = step_1d<T, POT>(x, c0, pb, cen, kr, mu_dt, amp, fma_t(w_prev, eta_prev, eta));
                 eta_prev = eta;
-                xg[k] = x;
-                if (record && alive && step <= 100000u) traj[step] = (double)x;
-                ++k;
-            }
+                if (record && alive && n <= 100000u) traj[n] = (double)x;
+                if (n == n_sample) {
+                    if (l == cnt) { xs[0] = x; es[0] = eta; qs = 0; }
+                    n_sample += every;
+                    ++cnt;
+                    if (traj || cnt == L) break;
+                }
+            } while (n < stop);
+        }
+        // fold the pending samples when the next tile's might not fit, and at the end
+        if (cnt == 0 || (cnt + per_tile <= L && n < n_end && !traj)) continue;
+        const double xi = (double)(qs < 2 ? (qs ? xs[1] : xs[0]) : (qs == 2 ? xs[2] : xs[3]));
+        const uint64_t bad = __ballot(l < cnt && (!isfinite(xi) || fabs(xi) > bound)) & group_mask;
+        bool mine = l < cnt && alive;
+        if (alive && bad) {
+            // frozen at its first bad sample: later ones are dropped, its state stays there
+            const int at = __ffsll((unsigned long long)(bad >> lane0)) - 1;
+            x_dead = (T)__shfl(xi, at, L);
+            eta_dead = __shfl(qs < 2 ? (qs ? es[1] : es[0]) : (qs == 2 ? es[2] : es[3]), at, L);
+            acc[A_BLOWN] = 1.0;
+            alive = false;
+            mine = mine && l < at;
+        }
+        const double d = mine ? xi - lam_w : 0.0;
+        const double ef = xi - ref_f, er = xi - ref_r;
+        const double f1 = cf * (ef - C.hf), f2 = cf * ef * ef, r1 = cr * (er - C.hr), r2 = cr * er * er;
+        const double af = mine && C.kind_f ? (C.kind_f == 1 ? f1 : f2) : -INFINITY;
+        const double ar = mine && C.kind_r ? (C.kind_r == 1 ? r1 : r2) : -INFINITY;
+        const double pf = group_prefix_max<L>(af), pr = group_prefix_max<L>(ar);
+        // the maximum before this sample, and after all
+        double mf = row_shr<1>(pf), mr = row_shr<1>(pr);
+        mf = l > 0 ? fmax(acc[A_MF], mf) : acc[A_MF];
+        mr = l > 0 ? fmax(acc[A_MR], mr) : acc[A_MR];
+        acc[A_MF] = fmax(acc[A_MF], group_bcast<L, L - 1>(pf));
+        acc[A_MR] = fmax(acc[A_MR], group_bcast<L, L - 1>(pr));
+        const double df = af - mf, dr = ar - mr;
+        const bool uf = df > 0.0, ur = dr > 0.0;
+        // no sample, or no step in this direction: alpha = 1, beta = 0
+        double tf = exp(-fabs(df)), tr = exp(-fabs(dr));
+        tf = mine && C.kind_f ? tf : 0.0;
+        tr = mine && C.kind_r ? tr : 0.0;
+        const double tf2 = tf * tf, tr2 = tr * tr;
+        double2 *ab = lds.ab + ab_place<L>((int)threadIdx.x);
+        ab[0] = double2{1.0, d};
+        ab[1] = double2{1.0, d * d};
+        ab[2] = double2{uf ? tf : 1.0, uf ? 1.0 : tf};
+        ab[3] = double2{uf ? tf2 : 1.0, uf ? 1.0 : tf2};
+        ab[4] = double2{ur ? tr : 1.0, ur ? 1.0 : tr};
+        ab[5] = double2{ur ? tr2 : 1.0, ur ? 1.0 : tr2};
+        wave_lds_sync();
+        // in sample order, so the sums do not depend on how the run is cut into launches
+        // (lanes without a sample left alpha = 1, beta = 0)
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) {
+            const double2 *ab_f = lds.ab + ab_place<L>(t0) + (i * L + l < kOrderedSums ? i * L + l : kOrderedSums - 1);
+            double2 v[L];
+#pragma unroll
+            for (int j = 0; j < L; ++j) v[j] = ab_f[7 * j];
+#pragma unroll
+            for (int j = 0; j < L; ++j) own[i] = fma(own[i], v[j].x, v[j].y);
         }
         wave_lds_sync();
-        // the tile's samples, one per lane (in passes of L where there are more)
-        for (uint32_t so = n_sample - base; so <= (uint32_t)hi;) {
-            const uint32_t o = so + lane_off;
-            const bool in = o <= (uint32_t)hi;
-            const int cnt = (int)__popcll(__ballot(in) & group_mask);
-            const double xi = in ? (double)xg[o] : 0.0;
-            bool mine = in && alive;
-            const uint64_t bad = __ballot(mine && (!isfinite(xi) || fabs(xi) > bound)) & group_mask;
-            if (bad) {
-                // frozen at its first bad sample: later ones are dropped, its state stays there
-                const int first = __ffsll((unsigned long long)(bad >> lane0)) - 1;
-                const uint32_t of = so + (first ? (uint32_t)first * every : 0u);
-                x_dead = xg[of]; eta_dead = zg[of];
-                acc[A_BLOWN] = 1.0;
-                alive = false;
-                mine = mine && l < first;
-            }
-            const double d = mine ? xi - lam_w : 0.0;
-            const double ef = xi - ref_f, er = xi - ref_r;
-            const double af = mine && C.kind_f ? (C.kind_f == 1 ? cf * (ef - C.hf) : cf * ef * ef) : -INFINITY;
-            const double ar = mine && C.kind_r ? (C.kind_r == 1 ? cr * (er - C.hr) : cr * er * er) : -INFINITY;
-            const double pf = group_prefix_max<L>(af), pr = group_prefix_max<L>(ar);
-            // the maximum before this sample
-            double mf = row_shr<1>(pf), mr = row_shr<1>(pr);
-            if constexpr (L > 16) {
-                const double bf = __shfl(pf, 15, L), br = __shfl(pr, 15, L);
-                mf = l == 16 ? bf : mf; mr = l == 16 ? br : mr;
-            }
-            mf = l > 0 ? fmax(acc[A_MF], mf) : acc[A_MF];
-            mr = l > 0 ? fmax(acc[A_MR], mr) : acc[A_MR];
-            acc[A_MF] = fmax(acc[A_MF], __shfl(pf, L - 1, L));
-            acc[A_MR] = fmax(acc[A_MR], __shfl(pr, L - 1, L));
-            const double df = af - mf, dr = ar - mr;
-            const bool uf = df > 0.0, ur = dr > 0.0;
-            // no sample, or no step in this direction: alpha = 1, beta = 0
-            const double tf = mine && C.kind_f ? exp(-fabs(df)) : 0.0, tr = mine && C.kind_r ? exp(-fabs(dr)) : 0.0;
-            const double tf2 = tf * tf, tr2 = tr * tr;
-            const double ab[kOrderedSums][2] = {{1.0, d}, {1.0, d * d},
-                                                {uf ? tf : 1.0, uf ? 1.0 : tf}, {uf ? tf2 : 1.0, uf ? 1.0 : tf2},
-                                                {ur ? tr : 1.0, ur ? 1.0 : tr}, {ur ? tr2 : 1.0, ur ? 1.0 : tr2}};
-#pragma unroll
-            for (int f = 0; f < kOrderedSums; ++f) { lds.ab[f][threadIdx.x][0] = ab[f][0]; lds.ab[f][threadIdx.x][1] = ab[f][1]; }
-            bool under = false, over = false;
-            if (mine) {
-                x_min = fmin(x_min, xi);
-                x_max = fmax(x_max, xi);
-                const double fb = floor((xi - xi_min) / xi_bin);
-                if (fb < 0.0) under = true;
-                else if (fb >= k_bins) over = true;
-                else if (lhist) atomicAdd(lhist + (int)fb, 1u);
-                else atomicAdd(hist_w + (int64_t)fb, 1ull);
-            }
-            acc[A_N] += (double)__popcll(__ballot(mine) & group_mask);
-            acc[A_UNDER] += (double)__popcll(__ballot(under) & group_mask);
-            acc[A_OVER] += (double)__popcll(__ballot(over) & group_mask);
-            wave_lds_sync();
-            // in sample order, so the sums do not depend on how the run is cut into launches
-#pragma unroll
-            for (int i = 0; i < kOwn; ++i) {
-                const int f = i * L + l < kOrderedSums ? i * L + l : kOrderedSums - 1;
-                const double *ab_f = &lds.ab[f][t0][0];
-#pragma unroll 4
-                for (int j = 0; j < cnt; ++j) own[i] = fma(own[i], ab_f[2 * j], ab_f[2 * j + 1]);
-            }
-            wave_lds_sync();
-            so += (uint32_t)cnt * every;
-            n_sample += (uint32_t)cnt * every;
+        bool under = false, over = false;
+        if (mine) {
+            x_min = fmin(x_min, xi);
+            x_max = fmax(x_max, xi);
+            const double fb = floor((xi - xi_min) / xi_bin);
+            if (fb < 0.0) under = true;
+            else if (fb >= k_bins) over = true;
+            else if (lhist) atomicAdd(lhist + (int)fb, 1u);
+            else atomicAdd(hist_w + (int64_t)fb, 1ull);
         }
-        n = stop;
+        acc[A_N] += (double)__popcll(__ballot(mine) & group_mask);
+        acc[A_UNDER] += (double)__popcll(__ballot(under) & group_mask);
+        acc[A_OVER] += (double)__popcll(__ballot(over) & group_mask);
+        cnt = 0;
     }
 #pragma unroll
     for (int off = 1; off < L; off <<= 1) {
@@ -449,12 +492,12 @@ __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int r
         }
 }
 
-template <typename T, int L, int Q>
+template <typename T, int L>
 __global__ __launch_bounds__(WG) void sim_1d(const DevProblem *__restrict__ probs, const WorkItem *__restrict__ items,
                                              int n_items, char *__restrict__ ws, int64_t step_begin,
                                              int64_t step_end, double *__restrict__ traj, int traj_rep, int lds_cap) {
     extern __shared__ unsigned int s_hist[];
-    __shared__ Lds1d<T, L, Q> lds;
+    __shared__ Lds1d lds;
     const int it = blockIdx.x;
     if (it >= n_items) return;
     const WorkItem item = items[it];
@@ -464,8 +507,8 @@ __global__ __launch_bounds__(WG) void sim_1d(const DevProblem *__restrict__ prob
     unsigned int *lhist = P.xi_nbins <= lds_cap ? s_hist : nullptr;
     if (lhist) lhist_clear(lhist, P.xi_nbins);
     if (r < item.n_reps) {
-        if (P.pot_kind == 0) sim_1d_replica<T, L, Q, 0>(P, w, item.rep_begin + r, ws, step_begin, step_end, traj, traj_rep, lhist, lds);
-        else sim_1d_replica<T, L, Q, 1>(P, w, item.rep_begin + r, ws, step_begin, step_end, traj, traj_rep, lhist, lds);
+        if (P.pot_kind == 0) sim_1d_replica<T, L, 0>(P, w, item.rep_begin + r, ws, step_begin, step_end, traj, traj_rep, lhist, lds);
+        else sim_1d_replica<T, L, 1>(P, w, item.rep_begin + r, ws, step_begin, step_end, traj, traj_rep, lhist, lds);
     }
     if (lhist) lhist_flush(lhist, P.xi_nbins, reinterpret_cast<unsigned long long *>(ws + P.off_hist) + (int64_t)w * P.xi_nbins);
 }

@@ -1,5 +1,5 @@
-"""The 1-D kernel's lane split (needs an MI355X): 32, 16, 8, 4, 2 lanes per replica
-(1 in fp32) by the number of replicas, normals drawn in tiles of 16 to 128 steps.
+"""The 1-D kernel's lane split (needs an MI355X): 16, 8, 4, 2 or 1 lanes per replica
+by the number of replicas, normals drawn in tiles of 64 down to 4 steps.
 
 A replica's trajectory and record depend on its number alone, so the first
 replicas of window 1 must come out the same bit for bit whatever the number of
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 # replicas per window (two windows): one size for each lane count, each ragged
-SIZES = [37, 1500, 3001, 5003, 14001, 33333]
+SIZES = [37, 3001, 5003, 33333, 66666]
 
 
 def _problem(replicas, precision, every, **kw):
@@ -48,7 +48,7 @@ def _records(prob, cuts=()):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
-@pytest.mark.parametrize("every", [1, 3, 10, 200])
+@pytest.mark.parametrize("every", [1, 3, 4, 10, 200])
 def test_records_do_not_depend_on_the_lane_split_or_the_launches(precision, every):
     print(f"case 1-D lanes {precision} every {every}", flush=True)
     # a bound near the well's edge freezes some of the replicas part way
@@ -64,7 +64,7 @@ def test_records_do_not_depend_on_the_lane_split_or_the_launches(precision, ever
             assert np.array_equal(a2[:SIZES[0]], acc[:SIZES[0]]), (n, cuts)
 
 
-@pytest.mark.parametrize("every", [1, 3, 10, 200])
+@pytest.mark.parametrize("every", [1, 3, 4, 10, 200])
 def test_records_match_the_oracle(every):
     print(f"case 1-D lanes against the oracle, every {every}", flush=True)
     p = _problem(SIZES[0], "fp64", every)
