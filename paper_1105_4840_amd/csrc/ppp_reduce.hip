@@ -109,26 +109,6 @@ __device__ __forceinline__ void step_terms(const DevProblem &P, const WinStat &s
     ga = fl + 0.5 * P.k * dl * dl * (1.0 - gamma2);
 }
 
-// Turn-on free energies from the records of window 1 (a1), window s (as) and
-// the unrestrained ensemble (a0); je_s = dF^JE(lambda_s) from the same records.
-struct TurnOn {
-    double eq5_first, eq6_first, eq5_last, eq6_last, eq10;
-};
-__device__ __forceinline__ TurnOn turn_on(const DevProblem &P, const double *a1, const double *as, const double *a0,
-                                          double je_s) {
-    TurnOn r;
-    // Eq. 5: DF = kT ln <exp(+beta k/2 (x - lambda)^2)> over the restrained window
-    r.eq5_first = P.kT * (lse_value(a1[A_MR], a1[A_SR]) - log(a1[A_N]));
-    r.eq5_last = P.kT * (lse_value(as[A_MF], as[A_SF]) - log(as[A_N]));
-    // Eq. 6: DF = -kT ln <exp(-beta k/2 (x_0 - lambda)^2)> over the free ensemble
-    r.eq6_first = -P.kT * (lse_value(a0[A_MF], a0[A_SF]) - log(a0[A_N]));
-    r.eq6_last = -P.kT * (lse_value(a0[A_MR], a0[A_SR]) - log(a0[A_N]));
-    // Eq. 10 factorised over x_0, x_1 .. x_s: the turn-on at lambda_1 from x_0, the
-    // steps, and the turn-off at lambda_s from x_s
-    r.eq10 = -P.beta * (r.eq6_first + je_s - r.eq5_last);
-    return r;
-}
-
 __device__ double block_sum(double v, double *sh) {
     const int t = threadIdx.x;
     sh[t] = v;
@@ -142,90 +122,448 @@ __device__ double block_sum(double v, double *sh) {
     return r;
 }
 
-__global__ __launch_bounds__(256) void k_estimators(const DevProblem *__restrict__ probs, char *__restrict__ ws) {
-    const DevProblem &P = probs[blockIdx.x];
-    __shared__ double sh[256];
-    const int s = P.n_windows, B = P.n_blocks, K = P.xi_nbins;
-    const int t = threadIdx.x;
+// Sum and extrema over a wavefront, in every lane.  The butterfly adds the lanes
+// 32, 16, 8, 4, 2, 1 apart; from 8 on the values repeat with that period, so a
+// rotation inside a row of 16 (a DPP move) brings the same partner as an
+// exchange through LDS would, six times sooner.
+template <int OFF> __device__ __forceinline__ double row_ror(double v) {
+    I2 w = __builtin_bit_cast(I2, v);
+    w.lo = __builtin_amdgcn_update_dpp(w.lo, w.lo, 0x120 + OFF, 0xf, 0xf, false);
+    w.hi = __builtin_amdgcn_update_dpp(w.hi, w.hi, 0x120 + OFF, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, w);
+}
+template <typename Op> __device__ __forceinline__ double wave_all(double v, Op op) {
+    v = op(v, __shfl_xor(v, 32));
+    v = op(v, __shfl_xor(v, 16));
+    v = op(v, row_ror<8>(v));
+    v = op(v, row_ror<4>(v));
+    v = op(v, row_ror<2>(v));
+    return op(v, row_ror<1>(v));
+}
+__device__ __forceinline__ double wave_sum(double v) { return wave_all(v, [](double a, double b) { return a + b; }); }
+__device__ __forceinline__ double wave_max(double v) { return wave_all(v, [](double a, double b) { return fmax(a, b); }); }
+
+// Sums of a workgroup of up to four wavefronts, in every thread.
+template <int NV>
+__device__ __forceinline__ void block_sum_vec(double (&v)[NV], double *sh) {
+    for (int q = 0; q < NV; ++q) v[q] = wave_sum(v[q]);
+    const int wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0)
+        for (int q = 0; q < NV; ++q) sh[q * 4 + wave] = v[q];
+    __syncthreads();
+    for (int q = 0; q < NV; ++q) {
+        double t = 0;
+        for (int u = 0; u < n_waves; ++u) t += sh[q * 4 + u];
+        v[q] = t;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Window totals and leave-one-out records of one window, by one wavefront.
+//
+// Lane l holds blocks [l c, (l + 1) c), c = ceil(B / 64).  A log-sum-exp without
+// block b is taken against the largest maximum among the others: the overall
+// maximum M, or for the block that holds it the next one; its sum is the sum of
+// the blocks before plus that of the blocks after, so nothing cancels.  Every
+// block then costs one exponential a direction instead of the B - 1 merges that
+// each leave-one-out record took when it was built by itself.
+// ---------------------------------------------------------------------------
+struct LseLoo {
+    double m, s, s2;          // all blocks: maximum, scaled sum, scaled sum of squares (of 2a)
+    double before, after;     // scaled sums of the blocks of the lanes before and after
+    double m_next, s_next;    // all blocks but the holder of the maximum
+    int holder;
+};
+
+__device__ __forceinline__ LseLoo lse_totals(const double *blk, int B, int b0, int b1, int fm) {
+    LseLoo r;
+    double mx = -INFINITY;
+    for (int b = b0; b < b1; ++b) mx = fmax(mx, blk[(int64_t)b * A_NFIELDS + fm]);
+    r.m = wave_max(mx);
+    int h = B;
+    for (int b = b1 - 1; b >= b0; --b)
+        if (blk[(int64_t)b * A_NFIELDS + fm] == r.m) h = b;
+    for (int off = 32; off >= 1; off >>= 1) h = min(h, __shfl_xor(h, off));
+    r.holder = h;
+    mx = -INFINITY;
+    for (int b = b0; b < b1; ++b)
+        if (b != h) mx = fmax(mx, blk[(int64_t)b * A_NFIELDS + fm]);
+    r.m_next = wave_max(mx);
+    double s = 0, s2 = 0, sn = 0;
+    for (int b = b0; b < b1; ++b) {
+        const double *a = blk + (int64_t)b * A_NFIELDS;
+        if (a[fm + 1] == 0.0) continue;                  // no sample in it
+        const double t = exp(a[fm] - r.m);
+        s += a[fm + 1] * t;
+        s2 += a[fm + 3] * (t * t);
+        if (b != h) sn += a[fm + 1] * exp(a[fm] - r.m_next);
+    }
+    double up = s, dn = s;                               // inclusive sums over the lanes
+    const int l = (int)threadIdx.x & 63;
+    for (int off = 1; off < 64; off <<= 1) {
+        const double u = __shfl_up(up, off), d = __shfl_down(dn, off);
+        if (l >= off) up += u;
+        if (l + off < 64) dn += d;
+    }
+    const double b_in = __shfl_up(up, 1), a_in = __shfl_down(dn, 1);
+    r.before = l > 0 ? b_in : 0.0;
+    r.after = l < 63 ? a_in : 0.0;
+    r.s = wave_sum(s);
+    r.s2 = wave_sum(s2);
+    r.s_next = wave_sum(sn);
+    return r;
+}
+
+// ln sum exp over every block but b, which is one of this lane's [b0, b1).
+__device__ __forceinline__ double lse_without(const LseLoo &r, const double *blk, int b0, int b1, int fm, int b) {
+    if (b == r.holder) return lse_value(r.m_next, r.s_next);
+    double s = r.before;
+    for (int c = b0; c < b1; ++c) {
+        const double *a = blk + (int64_t)c * A_NFIELDS;
+        if (c != b && a[fm + 1] != 0.0) s += a[fm + 1] * exp(a[fm] - r.m);
+    }
+    return lse_value(r.m, s + r.after);
+}
+
+// Statistics of one window (everything that needs only its own record and its
+// neighbour's histogram), its terms of every profile and of every leave-one-out
+// profile, and its least-squares Gaussian; k_profiles sums the terms over the
+// windows.  One workgroup per window.
+//
+// The paper's sigma_i (Sec. IV A: gamma_i^2 = k sigma_i^2 / kT with sigma_i by
+// least-squares fitting of the x_i distribution): the Gaussian A exp(-(x -
+// mu)^2 / (2 sigma^2)) closest in least squares to the histogram density
+// count_b / (n dxi) at the bin centres, by Levenberg-Marquardt from the sample
+// moments.
+//
+// Bound: the fp64 exponentials of the fit, on one CU a window.  A step's
+// exponentials serve its cost and, once it is accepted, the next step's
+// Jacobian (16 bins a thread are kept in registers); a rejected step leaves the
+// normal equations as they are; a trial equal to the one just rejected is not
+// evaluated again (damping far below 1 does not move it); and bins that are
+// empty and more than 13 sigma from the mean (a square below 1e-73 of the peak's)
+// are left out.
+constexpr int kFitKeep = 16;
+
+__global__ __launch_bounds__(256) void k_windows(const DevProblem *__restrict__ probs, char *__restrict__ ws) {
+    const DevProblem &P = probs[blockIdx.y];
+    const int s = P.n_windows, S = P.n_sim_windows, B = P.n_blocks, K = P.xi_nbins;
+    const int w = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (w >= S) return;
+    __shared__ double sh[10 * 4];
+    __shared__ double s_tot[A_NFIELDS];
+    __shared__ double s_n_next;
+    __shared__ int s_range[2];
     const double *lam = dptr(ws, P.off_lambda);
-    const double *blk = dptr(ws, P.off_blk);
-    double *tot = dptr(ws, P.off_tot);
+    const double *blk = dptr(ws, P.off_blk) + (int64_t)w * B * A_NFIELDS;
     double *out = dptr(ws, P.off_out);
     double *jack = dptr(ws, P.off_jack);
-    const unsigned long long *hist = reinterpret_cast<const unsigned long long *>(ws + P.off_hist);
+    const unsigned long long *hist = reinterpret_cast<const unsigned long long *>(ws + P.off_hist) + (int64_t)w * K;
 #define OUT(f, i) out[(int64_t)(f) * s + (i)]
+    if (t == 0) { s_range[0] = K; s_range[1] = -1; }
+    __syncthreads();
 
-    const int S = P.n_sim_windows;
-    // (a) window totals: blocks merged in block order
-    for (int w = t; w < S; w += blockDim.x) {
+    if (wave == 0) {
+        const int chunk = (B + 63) / 64;
+        const int b0 = min(B, lane * chunk), b1 = min(B, b0 + chunk);
+        double n = 0, s1 = 0, s2 = 0, lo = INFINITY, hi = -INFINITY, un = 0, ov = 0, bl = 0;
+        for (int b = b0; b < b1; ++b) {
+            const double *a = blk + (int64_t)b * A_NFIELDS;
+            n += a[A_N]; s1 += a[A_S1]; s2 += a[A_S2];
+            lo = fmin(lo, a[A_XMIN]); hi = fmax(hi, a[A_XMAX]);
+            un += a[A_UNDER]; ov += a[A_OVER]; bl += a[A_BLOWN];
+        }
         double a[A_NFIELDS];
-        acc_empty(a);
-        for (int b = 0; b < B; ++b) acc_merge(a, blk + ((int64_t)w * B + b) * A_NFIELDS);
-        for (int f = 0; f < A_NFIELDS; ++f) tot[(int64_t)w * A_NFIELDS + f] = a[f];
+        a[A_N] = wave_sum(n); a[A_S1] = wave_sum(s1); a[A_S2] = wave_sum(s2);
+        a[A_XMIN] = -wave_max(-lo); a[A_XMAX] = wave_max(hi);
+        a[A_UNDER] = wave_sum(un); a[A_OVER] = wave_sum(ov); a[A_BLOWN] = wave_sum(bl);
+        const LseLoo F = lse_totals(blk, B, b0, b1, A_MF), R = lse_totals(blk, B, b0, b1, A_MR);
+        a[A_MF] = F.m; a[A_SF] = F.s; a[A_MF2] = 2.0 * F.m; a[A_SF2] = F.s2;
+        a[A_MR] = R.m; a[A_SR] = R.s; a[A_MR2] = 2.0 * R.m; a[A_SR2] = R.s2;
+        if (lane == 0) {
+            double *tot = dptr(ws, P.off_tot) + (int64_t)w * A_NFIELDS;
+            for (int f = 0; f < A_NFIELDS; ++f) { tot[f] = a[f]; s_tot[f] = a[f]; }
+        }
+        if (lane == 0 && w < s) {
+            const WinStat st = win_stat(a, lam[w]);
+            OUT(O_XI_MEAN, w) = st.mean;
+            OUT(O_XI_STD, w) = sqrt(st.var);
+            OUT(O_GAMMA2, w) = P.k * st.var / P.kT;
+            OUT(O_XI_MINS, w) = a[A_XMIN];
+            OUT(O_XI_MAXS, w) = a[A_XMAX];
+            OUT(O_LSE_FWD, w) = w + 1 < s ? st.lse_f : NAN;
+            OUT(O_LSE_REV, w) = w > 0 ? st.lse_r : NAN;
+            OUT(O_N_SAMPLES, w) = a[A_N];
+            OUT(O_N_BLOWN, w) = a[A_BLOWN];
+            OUT(O_UNDER, w) = a[A_UNDER];
+            OUT(O_OVER, w) = a[A_OVER];
+            // this window's term of the reverse profile at w and of the others at w + 1
+            OUT(O_DF_REV, w) = w > 0 ? P.kT * (st.lse_r - log(st.n)) : 0.0;
+            if (w + 1 < s) {
+                const double dl = lam[w + 1] - lam[w];
+                OUT(O_KISH, w) = exp(2.0 * st.lse_f - lse_value(a[A_MF2], a[A_SF2])) / st.n;
+                OUT(O_DL_SIGMA, w) = fabs(dl) / sqrt(st.var);
+                const double reach = dl > 0 ? a[A_XMAX] - st.mean : st.mean - a[A_XMIN];
+                OUT(O_DL_REACH, w) = fabs(dl) / reach;
+                OUT(O_CRIT, w) = fabs(dl) <= reach ? 1.0 : 0.0;
+                double dje, dfl, dga;
+                step_terms(P, st, lam[w], lam[w + 1], dje, dfl, dga);
+                OUT(O_DF_JE, w + 1) = dje; OUT(O_DF_FLUCT, w + 1) = dfl; OUT(O_DF_GAUSS, w + 1) = dga;
+                OUT(O_DF_FLUCT_LIT, w + 1) = lam[w] - st.mean;
+                OUT(O_DF_GAUSS_LIT, w + 1) = 1.0 - P.k * st.var / P.kT;
+            } else {
+                OUT(O_KISH, w) = NAN; OUT(O_DL_SIGMA, w) = NAN; OUT(O_DL_REACH, w) = NAN; OUT(O_CRIT, w) = NAN;
+                OUT(O_OVL, w) = NAN;
+            }
+        }
+        // block b removed from every window: this window's terms without it
+        if (B > 1)
+            for (int b = b0; b < b1; ++b) {
+                const double *c = blk + (int64_t)b * A_NFIELDS;
+                const double ln = log(a[A_N] - c[A_N]);
+                if (w + 1 < s) {
+                    double q[A_NFIELDS];
+                    q[A_N] = a[A_N] - c[A_N]; q[A_S1] = a[A_S1] - c[A_S1]; q[A_S2] = a[A_S2] - c[A_S2];
+                    WinStat st;
+                    const double m1 = q[A_S1] / q[A_N];
+                    st.n = q[A_N];
+                    st.mean = lam[w] + m1;
+                    st.var = (q[A_S2] - q[A_N] * m1 * m1) / (q[A_N] - 1.0);
+                    st.lse_f = lse_without(F, blk, b0, b1, A_MF, b);
+                    double dje, dfl, dga;
+                    step_terms(P, st, lam[w], lam[w + 1], dje, dfl, dga);
+                    double *jb = jack + (int64_t)b * JK_FIELDS * s;
+                    jb[0 * s + w + 1] = dje; jb[1 * s + w + 1] = dfl; jb[2 * s + w + 1] = dga;
+                }
+                if (P.free_ens) {
+                    // Eq. 5 from the ends, Eq. 6 from the free ensemble
+                    double *jt = dptr(ws, P.off_jack_turn) + (int64_t)b * JK_TURN;
+                    if (w == 0) jt[0] = P.kT * (lse_without(R, blk, b0, b1, A_MR, b) - ln);
+                    if (w == s - 1) jt[2] = P.kT * (lse_without(F, blk, b0, b1, A_MF, b) - ln);
+                    if (w == s) {
+                        jt[1] = -P.kT * (lse_without(F, blk, b0, b1, A_MF, b) - ln);
+                        jt[3] = -P.kT * (lse_without(R, blk, b0, b1, A_MR, b) - ln);
+                    }
+                }
+            }
+    } else {
+        // meanwhile the other wavefronts find the range of non-empty bins, and
+        // wavefront 1 the sample count of the next window
+        int lo = K, hi = -1;
+        for (int b = t - 64; b < K; b += 192)
+            if (hist[b]) { lo = min(lo, b); hi = b; }
+        for (int off = 32; off >= 1; off >>= 1) {
+            lo = min(lo, __shfl_xor(lo, off));
+            hi = max(hi, __shfl_xor(hi, off));
+        }
+        if (lane == 0 && hi >= 0) { atomicMin(&s_range[0], lo); atomicMax(&s_range[1], hi); }
+        if (wave == 1 && w + 1 < s) {
+            double nn = 0;
+            for (int b = lane; b < B; b += 64) nn += blk[(int64_t)(B + b) * A_NFIELDS + A_N];
+            nn = wave_sum(nn);
+            if (lane == 0) s_n_next = nn;
+        }
     }
     __syncthreads();
-    // (b) per-window statistics
-    for (int w = t; w < s; w += blockDim.x) {
-        const double *a = tot + (int64_t)w * A_NFIELDS;
-        const WinStat st = win_stat(a, lam[w]);
-        OUT(O_XI_MEAN, w) = st.mean;
-        OUT(O_XI_STD, w) = sqrt(st.var);
-        OUT(O_GAMMA2, w) = P.k * st.var / P.kT;
-        OUT(O_XI_MINS, w) = a[A_XMIN];
-        OUT(O_XI_MAXS, w) = a[A_XMAX];
-        OUT(O_LSE_FWD, w) = w + 1 < s ? st.lse_f : NAN;
-        OUT(O_LSE_REV, w) = w > 0 ? st.lse_r : NAN;
-        OUT(O_N_SAMPLES, w) = a[A_N];
-        OUT(O_N_BLOWN, w) = a[A_BLOWN];
-        OUT(O_UNDER, w) = a[A_UNDER];
-        OUT(O_OVER, w) = a[A_OVER];
-        if (w + 1 < s) {
-            const double dl = lam[w + 1] - lam[w];
-            OUT(O_KISH, w) = exp(2.0 * st.lse_f - lse_value(a[A_MF2], a[A_SF2])) / st.n;
-            OUT(O_DL_SIGMA, w) = fabs(dl) / sqrt(st.var);
-            const double reach = dl > 0 ? a[A_XMAX] - st.mean : st.mean - a[A_XMIN];
-            OUT(O_DL_REACH, w) = fabs(dl) / reach;
-            OUT(O_CRIT, w) = fabs(dl) <= reach ? 1.0 : 0.0;
+    if (w >= s) return;
+    const double n = s_tot[A_N];
+    const int e_lo = s_range[0], e_hi = s_range[1];
+    // overlap of adjacent histograms: sum_b min(rho_i(b), rho_{i+1}(b))
+    if (w + 1 < s) {
+        double part[1] = {0.0};
+        // (a window without samples gives 0 / 0 in every bin, and fmin then takes the neighbour's)
+        for (int b = (n > 0.0 ? e_lo : 0) + t; b <= (n > 0.0 ? e_hi : K - 1); b += 256)
+            part[0] += fmin((double)hist[b] / n, (double)hist[K + b] / s_n_next);
+        block_sum_vec<1>(part, sh);
+        if (t == 0) OUT(O_OVL, w) = part[0];
+    }
+
+    const double m1 = s_tot[A_S1] / n;
+    const double var = (s_tot[A_S2] - n * m1 * m1) / (n - 1.0);
+    double nz[1] = {0.0};                             // non-empty bins
+    for (int b = e_lo + t; b <= e_hi; b += 256) nz[0] += hist[b] ? 1.0 : 0.0;
+    block_sum_vec<1>(nz, sh);
+    if (!(n > 2.0) || !(var > 0.0) || nz[0] < 3.0) {   // three parameters need three points
+        if (t == 0) { OUT(O_SIGMA_LSQ, w) = NAN; OUT(O_GAMMA2_LSQ, w) = NAN; }
+        return;
+    }
+    const double norm = 1.0 / (n * P.xi_bin);
+    const double x0 = P.xi_min, xb = P.xi_bin;
+    // parameters, damping, squared residual and normal equations (J^T J, J^T r) of the accepted point
+    double A = 1.0 / (sqrt(var) * 2.5066282746310002), mu = lam[w] + m1, sg = sqrt(var);
+    double lm = 1e-3, c0 = 0.0;
+    double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    double ke[kFitKeep];
+    int first = 0, last = 0;                           // this point's bins, from a multiple of 256
+    auto bins_of = [&](double pm, double ps) {
+        const double a = floor((pm - 13.0 * ps - x0) / xb), z = ceil((pm + 13.0 * ps - x0) / xb);
+        const int ia = a > (double)e_lo ? e_lo : (a < 0.0 ? 0 : (int)a);
+        const int iz = z < (double)e_hi ? e_hi : (z > (double)(K - 1) ? K - 1 : (int)z);
+        // (a NaN keeps every bin)
+        first = a == a ? ia & ~255 : 0;
+        last = z == z ? iz : K - 1;
+    };
+    // squared residual of (pA, pm, ps); the exponentials of the thread's first bins stay in ke
+    auto cost = [&](double pA, double pm, double ps) {
+        bins_of(pm, ps);
+        double c[1] = {0.0};
+        const double i2 = 1.0 / (2.0 * ps * ps);
+        auto bin = [&](int b) {
+            const double d = x0 + ((double)b + 0.5) * xb - pm;
+            const double e = exp(-d * d * i2);
+            const double r = (double)hist[b] * norm - pA * e;
+            c[0] += r * r;
+            return e;
+        };
+#pragma unroll
+        for (int i = 0; i < kFitKeep; ++i) {
+            const int b = first + t + 256 * i;
+            if (b <= last) ke[i] = bin(b);
+        }
+        for (int b = first + t + 256 * kFitKeep; b <= last; b += 256) bin(b);
+        block_sum_vec<1>(c, sh);
+        return c[0];
+    };
+    auto normal_equations = [&]() {
+        for (int q = 0; q < 9; ++q) v[q] = 0.0;
+        const double i2 = 1.0 / (2.0 * sg * sg), is2 = 1.0 / (sg * sg);
+        auto bin = [&](int b, double e, double d) {
+            const double f = A * e;
+            const double r = (double)hist[b] * norm - f;
+            const double jA = e, jm = f * d * is2, js = f * d * d * is2 / sg;
+            v[0] += jA * jA; v[1] += jA * jm; v[2] += jA * js;
+            v[3] += jm * jm; v[4] += jm * js; v[5] += js * js;
+            v[6] += jA * r; v[7] += jm * r; v[8] += js * r;
+        };
+#pragma unroll
+        for (int i = 0; i < kFitKeep; ++i) {
+            const int b = first + t + 256 * i;
+            if (b <= last) bin(b, ke[i], x0 + ((double)b + 0.5) * xb - mu);
+        }
+        for (int b = first + t + 256 * kFitKeep; b <= last; b += 256) {
+            const double d = x0 + ((double)b + 0.5) * xb - mu;
+            bin(b, exp(-d * d * i2), d);
+        }
+        block_sum_vec<9>(v, sh);
+    };
+    c0 = cost(A, mu, sg);
+    normal_equations();
+    double tA = NAN, tm = NAN, ts = NAN;               // the trial rejected last
+    for (int it = 0; it < 200; ++it) {
+        // (J^T J + lm diag) delta = J^T r, by Cramer's rule on the 3x3 system (in every thread)
+        const double a00 = v[0] * (1 + lm), a11 = v[3] * (1 + lm), a22 = v[5] * (1 + lm);
+        const double a01 = v[1], a02 = v[2], a12 = v[4];
+        const double det = a00 * (a11 * a22 - a12 * a12) - a01 * (a01 * a22 - a12 * a02) + a02 * (a01 * a12 - a11 * a02);
+        const double g0 = v[6], g1 = v[7], g2 = v[8];
+        const double d0 = (g0 * (a11 * a22 - a12 * a12) - a01 * (g1 * a22 - a12 * g2) + a02 * (g1 * a12 - a11 * g2)) / det;
+        const double d1 = (a00 * (g1 * a22 - a12 * g2) - g0 * (a01 * a22 - a12 * a02) + a02 * (a01 * g2 - g1 * a02)) / det;
+        const double d2 = (a00 * (a11 * g2 - g1 * a12) - a01 * (a01 * g2 - g1 * a02) + g0 * (a01 * a12 - a11 * a02)) / det;
+        const double nA = A + d0, nm = mu + d1, ns = fabs(sg + d2);
+        const bool done = fabs(d0) <= 1e-14 * fabs(A) && fabs(d1) <= 1e-14 * (fabs(mu) + sg) && fabs(d2) <= 1e-14 * sg;
+        if (nA == tA && nm == tm && ns == ts) {
+            lm *= 10.0;
         } else {
-            OUT(O_KISH, w) = NAN; OUT(O_DL_SIGMA, w) = NAN; OUT(O_DL_REACH, w) = NAN; OUT(O_CRIT, w) = NAN;
+            const double c1 = cost(nA, nm, ns);
+            if (c1 <= c0) {
+                A = nA; mu = nm; sg = ns; c0 = c1; lm = fmax(lm * 0.1, 1e-15);
+                tA = NAN;
+                if (!done && lm <= 1e12) normal_equations();
+            } else {
+                lm *= 10.0;
+                tA = nA; tm = nm; ts = ns;
+            }
+        }
+        if (done || lm > 1e12) break;
+    }
+    if (t == 0) {
+        OUT(O_SIGMA_LSQ, w) = sg;
+        OUT(O_GAMMA2_LSQ, w) = P.k * sg * sg / P.kT;
+    }
+#undef OUT
+}
+
+// Running sums of a row of s terms in place, eight loads at a time.
+__device__ __forceinline__ void prefix_row(double *row, int s) {
+    double acc = 0.0;
+    row[0] = 0.0;
+    for (int j0 = 1; j0 < s; j0 += 8) {
+        double v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = j0 + i < s ? row[j0 + i] : 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            acc += v[i];
+            if (j0 + i < s) row[j0 + i] = acc;
         }
     }
+}
+
+// Jackknife standard error of value(b) over the B blocks.
+template <typename Fn> __device__ __forceinline__ double jack_se(int B, Fn &&value) {
+    if (B <= 1) return NAN;
+    double m = 0;
+#pragma unroll 8
+    for (int b = 0; b < B; ++b) m += value(b);
+    m /= B;
+    double ss = 0;
+#pragma unroll 8
+    for (int b = 0; b < B; ++b) {
+        const double d = value(b) - m;
+        ss += d * d;
+    }
+    return sqrt((B - 1.0) / B * ss);
+}
+
+// Profiles: the windows' terms summed along lambda, their leave-one-out twins and
+// standard errors, and the turn-on free energies.  One workgroup per problem.
+__global__ __launch_bounds__(256) void k_profiles(const DevProblem *__restrict__ probs, char *__restrict__ ws) {
+    const DevProblem &P = probs[blockIdx.x];
+    const int s = P.n_windows, B = P.n_blocks, t = threadIdx.x;
+    const double *lam = dptr(ws, P.off_lambda);
+    const double *tot = dptr(ws, P.off_tot);
+    double *out = dptr(ws, P.off_out);
+    double *jack = dptr(ws, P.off_jack);
+    double *turn = dptr(ws, P.off_turn);
+    double *jt = dptr(ws, P.off_jack_turn);
+    __shared__ double s_eq5_first;
+#define OUT(f, i) out[(int64_t)(f) * s + (i)]
+    // one thread per row of terms; the least-squares Gaussians' row of Eq. 13 is formed first
+    for (int j = t; j < s; j += 256) {
+        double g = 0.0;
+        if (j > 0) {
+            // Eq. 13 with gamma_i^2 from the fitted sigma_i, <x_i> the sample mean
+            const double dl = lam[j] - lam[j - 1];
+            const double mean = OUT(O_XI_MEAN, j - 1), g2 = OUT(O_GAMMA2_LSQ, j - 1);
+            g = P.k * dl * (lam[j - 1] - mean) + 0.5 * P.k * dl * dl * (1.0 - g2);
+        }
+        OUT(O_DF_GAUSS_LSQ, j) = g;
+    }
     __syncthreads();
-    // (c) profiles: prefix sums over the steps
+    const int rows[7] = {O_DF_JE, O_DF_FLUCT, O_DF_GAUSS, O_DF_REV, O_DF_FLUCT_LIT, O_DF_GAUSS_LIT, O_DF_GAUSS_LSQ};
+    for (int q = t; q < 7 + (B > 1 ? 3 * B : 0); q += 256) {
+        if (q < 7) prefix_row(&OUT(rows[q], 0), s);
+        else prefix_row(jack + ((int64_t)((q - 7) / 3) * JK_FIELDS + (q - 7) % 3) * s, s);
+    }
+    __syncthreads();
+    // Turn-on free energies from the records of window 1 (a1), window s (as) and the
+    // unrestrained ensemble (a0).
+    // Eq. 5: DF = kT ln <exp(+beta k/2 (x - lambda)^2)> over the restrained window
+    // Eq. 6: DF = -kT ln <exp(-beta k/2 (x_0 - lambda)^2)> over the free ensemble
+    // Eq. 10 factorised over x_0, x_1 .. x_s: the turn-on at lambda_1 from x_0, the
+    // steps, and the turn-off at lambda_s from x_s
     if (t == 0) {
-        double je = 0, fl = 0, ga = 0, rev = 0;
-        double s1 = 0, s2 = 0;   // sums over i < j of (lambda_i - <x_i>) and (1 - gamma_i^2)
-        OUT(O_DF_JE, 0) = 0; OUT(O_DF_FLUCT, 0) = 0; OUT(O_DF_GAUSS, 0) = 0; OUT(O_DF_REV, 0) = 0;
-        OUT(O_DF_FLUCT_LIT, 0) = 0; OUT(O_DF_GAUSS_LIT, 0) = 0;
-        for (int j = 1; j < s; ++j) {
-            const WinStat st = win_stat(tot + (int64_t)(j - 1) * A_NFIELDS, lam[j - 1]);
-            double dje, dfl, dga;
-            step_terms(P, st, lam[j - 1], lam[j], dje, dfl, dga);
-            je += dje; fl += dfl; ga += dga;
-            // Eqs. 14 and 13 as printed, lambda_j taken as the end point of j + 1 windows
-            s1 += lam[j - 1] - st.mean;
-            s2 += 1.0 - P.k * st.var / P.kT;
-            const double span = lam[j] - lam[0], npts = (double)(j + 1);
-            const double fl_lit = P.k * span * s1 / npts;
-            OUT(O_DF_FLUCT_LIT, j) = fl_lit;
-            OUT(O_DF_GAUSS_LIT, j) = P.k * span * span / (2.0 * npts) * s2 / npts + fl_lit;
-            const WinStat sj = win_stat(tot + (int64_t)j * A_NFIELDS, lam[j]);
-            rev += P.kT * (sj.lse_r - log(sj.n));
-            OUT(O_DF_JE, j) = je; OUT(O_DF_FLUCT, j) = fl; OUT(O_DF_GAUSS, j) = ga; OUT(O_DF_REV, j) = rev;
-        }
-        for (int j = 0; j < s; ++j) {
-            OUT(O_DF_COM, j) = 0.5 * (OUT(O_DF_JE, j) + OUT(O_DF_FLUCT, j));
-            OUT(O_DF_UNC, j) = 0.5 * (OUT(O_DF_JE, j) - OUT(O_DF_FLUCT, j));
-        }
-        double *turn = dptr(ws, P.off_turn);
         if (P.free_ens) {
             const double *a1 = tot, *as = tot + (int64_t)(s - 1) * A_NFIELDS, *a0 = tot + (int64_t)s * A_NFIELDS;
-            const TurnOn on = turn_on(P, a1, as, a0, OUT(O_DF_JE, s - 1));
-            turn[PPP_ON_EQ5_FIRST] = on.eq5_first;
-            turn[PPP_ON_EQ6_FIRST] = on.eq6_first;
-            turn[PPP_ON_EQ5_LAST] = on.eq5_last;
-            turn[PPP_ON_EQ6_LAST] = on.eq6_last;
-            turn[PPP_ON_EQ10_LOG] = on.eq10;
+            const double eq5_first = P.kT * (lse_value(a1[A_MR], a1[A_SR]) - log(a1[A_N]));
+            const double eq5_last = P.kT * (lse_value(as[A_MF], as[A_SF]) - log(as[A_N]));
+            const double eq6_first = -P.kT * (lse_value(a0[A_MF], a0[A_SF]) - log(a0[A_N]));
+            const double eq6_last = -P.kT * (lse_value(a0[A_MR], a0[A_SR]) - log(a0[A_N]));
+            turn[PPP_ON_EQ5_FIRST] = eq5_first;
+            turn[PPP_ON_EQ6_FIRST] = eq6_first;
+            turn[PPP_ON_EQ5_LAST] = eq5_last;
+            turn[PPP_ON_EQ6_LAST] = eq6_last;
+            turn[PPP_ON_EQ10_LOG] = -P.beta * (eq6_first + OUT(O_DF_JE, s - 1) - eq5_last);
             // Eq. 7: <k/2 (x - lambda)^2> over the restrained window and over x_0
             const double dls = lam[s - 1] - lam[0];
             turn[PPP_ON_LOWER_FIRST] = 0.5 * P.k * a1[A_S2] / a1[A_N];
@@ -239,233 +577,53 @@ __global__ __launch_bounds__(256) void k_estimators(const DevProblem *__restrict
             turn[PPP_ON_FREE_STD] = sqrt(f0.var);
             turn[PPP_ON_FREE_UNDER] = a0[A_UNDER];
             turn[PPP_ON_FREE_OVER] = a0[A_OVER];
-            for (int j = 0; j < s; ++j) OUT(O_G, j) = OUT(O_DF_JE, j) - on.eq5_first;   // Eq. 15
+            s_eq5_first = eq5_first;
         } else {
             for (int f = 0; f < PPP_ON_NFIELDS; ++f) turn[f] = NAN;
-            for (int j = 0; j < s; ++j) OUT(O_G, j) = NAN;
+            s_eq5_first = NAN;
         }
     }
-    // (d) jackknife: block b removed from every window.  First every (block,
-    // step) term from its window without that block, in parallel; then the
-    // prefix sums per block.  Blocks are merged in block order as before.
-    auto loo = [&](int b, int w, double *a) {
-        acc_empty(a);
-        for (int c = 0; c < B; ++c)
-            if (c != b) acc_merge(a, blk + ((int64_t)w * B + c) * A_NFIELDS);
-    };
-    if (B > 1) {
-        for (int q = t; q < B * (s - 1); q += blockDim.x) {
-            const int b = q / (s - 1), j = q % (s - 1) + 1;
-            double a[A_NFIELDS];
-            loo(b, j - 1, a);
-            const WinStat st = win_stat(a, lam[j - 1]);
-            double dje, dfl, dga;
-            step_terms(P, st, lam[j - 1], lam[j], dje, dfl, dga);
-            double *jb = jack + (int64_t)b * JK_FIELDS * s;
-            jb[0 * s + j] = dje; jb[1 * s + j] = dfl; jb[2 * s + j] = dga;
-        }
-        __syncthreads();
-        for (int b = t; b < B; b += blockDim.x) {
-            double je = 0, fl = 0, ga = 0;
-            double *jb = jack + (int64_t)b * JK_FIELDS * s;
-            jb[0 * s] = 0; jb[1 * s] = 0; jb[2 * s] = 0; jb[3 * s] = 0;
-            for (int j = 1; j < s; ++j) {
-                je += jb[0 * s + j]; fl += jb[1 * s + j]; ga += jb[2 * s + j];
-                jb[0 * s + j] = je; jb[1 * s + j] = fl; jb[2 * s + j] = ga; jb[3 * s + j] = 0.5 * (je + fl);
-            }
-            if (P.free_ens) {
-                double a1[A_NFIELDS], as[A_NFIELDS], a0[A_NFIELDS];
-                loo(b, 0, a1);
-                loo(b, s - 1, as);
-                loo(b, s, a0);
-                const TurnOn on = turn_on(P, a1, as, a0, je);
-                double *jt = dptr(ws, P.off_jack_turn) + (int64_t)b * JK_TURN;
-                jt[0] = on.eq5_first; jt[1] = on.eq6_first; jt[2] = on.eq5_last; jt[3] = on.eq6_last; jt[4] = on.eq10;
-                for (int j = 0; j < s; ++j) jb[4 * s + j] = jb[0 * s + j] - on.eq5_first;
-            } else {
-                for (int j = 0; j < s; ++j) jb[4 * s + j] = NAN;
-            }
-        }
-    }
+    if (P.free_ens && B > 1)
+        for (int b = t; b < B; b += 256)
+            jt[b * JK_TURN + 4] = -P.beta * (jt[b * JK_TURN + 1] + jack[(int64_t)b * JK_FIELDS * s + s - 1] - jt[b * JK_TURN + 2]);
     __syncthreads();
-    if (t == 0 && P.free_ens) {
-        const int fields[JK_TURN] = {PPP_ON_EQ5_FIRST_SE, PPP_ON_EQ6_FIRST_SE, PPP_ON_EQ5_LAST_SE,
-                                     PPP_ON_EQ6_LAST_SE, PPP_ON_EQ10_LOG_SE};
-        const double *jt = dptr(ws, P.off_jack_turn);
-        double *turn = dptr(ws, P.off_turn);
-        for (int q = 0; q < JK_TURN; ++q) {
-            double se = NAN;
-            if (B > 1) {
-                double m = 0;
-                for (int b = 0; b < B; ++b) m += jt[b * JK_TURN + q];
-                m /= B;
-                double ss = 0;
-                for (int b = 0; b < B; ++b) {
-                    const double d = jt[b * JK_TURN + q] - m;
-                    ss += d * d;
-                }
-                se = sqrt((B - 1.0) / B * ss);
-            }
-            turn[fields[q]] = se;
+    for (int j = t; j < s; j += 256) {
+        const double je = OUT(O_DF_JE, j), fl = OUT(O_DF_FLUCT, j);
+        OUT(O_DF_COM, j) = 0.5 * (je + fl);
+        OUT(O_DF_UNC, j) = 0.5 * (je - fl);
+        OUT(O_G, j) = je - s_eq5_first;                // Eq. 15; NaN without the free ensemble
+        if (j > 0) {
+            // Eqs. 14 and 13 as printed, lambda_j taken as the end point of j + 1 windows
+            const double span = lam[j] - lam[0], npts = (double)(j + 1);
+            const double fl_lit = P.k * span * OUT(O_DF_FLUCT_LIT, j) / npts;
+            OUT(O_DF_GAUSS_LIT, j) = P.k * span * span / (2.0 * npts) * OUT(O_DF_GAUSS_LIT, j) / npts + fl_lit;
+            OUT(O_DF_FLUCT_LIT, j) = fl_lit;
         }
     }
-    for (int j = t; j < s; j += blockDim.x) {
-        const int fields[JK_FIELDS] = {O_DF_JE_SE, O_DF_FLUCT_SE, O_DF_GAUSS_SE, O_DF_COM_SE, O_G_SE};
-        for (int q = 0; q < JK_FIELDS; ++q) {
-            double se = NAN;
-            if (B > 1) {
-                double m = 0;
-                for (int b = 0; b < B; ++b) m += jack[((int64_t)b * JK_FIELDS + q) * s + j];
-                m /= B;
-                double ss = 0;
-                for (int b = 0; b < B; ++b) {
-                    const double d = jack[((int64_t)b * JK_FIELDS + q) * s + j] - m;
-                    ss += d * d;
-                }
-                se = sqrt((B - 1.0) / B * ss);
-            }
-            OUT(fields[q], j) = se;
+    const int se[JK_FIELDS] = {O_DF_JE_SE, O_DF_FLUCT_SE, O_DF_GAUSS_SE, O_DF_COM_SE, O_G_SE};
+    for (int q = t; q < JK_FIELDS * s + (P.free_ens ? JK_TURN : 0); q += 256) {
+        if (q >= JK_FIELDS * s) {
+            const int f = q - JK_FIELDS * s;
+            const int fields[JK_TURN] = {PPP_ON_EQ5_FIRST_SE, PPP_ON_EQ6_FIRST_SE, PPP_ON_EQ5_LAST_SE,
+                                         PPP_ON_EQ6_LAST_SE, PPP_ON_EQ10_LOG_SE};
+            turn[fields[f]] = jack_se(B, [&](int b) { return jt[b * JK_TURN + f]; });
+            continue;
         }
-    }
-    // (e) overlap of adjacent histograms: sum_b min(rho_i(b), rho_{i+1}(b)), one
-    // wavefront per adjacent pair (lanes stride the bins, then a fixed tree)
-    {
-        const int wave = t >> 6, lane = t & 63, n_waves = blockDim.x >> 6;
-        for (int i = wave; i + 1 < s; i += n_waves) {
-            const double ni = tot[(int64_t)i * A_NFIELDS + A_N], nj = tot[(int64_t)(i + 1) * A_NFIELDS + A_N];
-            double part = 0;
-            for (int b = lane; b < K; b += 64)
-                part += fmin((double)hist[(int64_t)i * K + b] / ni, (double)hist[(int64_t)(i + 1) * K + b] / nj);
-            for (int off = 32; off >= 1; off >>= 1) part += __shfl_xor(part, off);
-            if (lane == 0) OUT(O_OVL, i) = part;
-        }
-        if (t == 0) OUT(O_OVL, s - 1) = NAN;
+        const int f = q / s, j = q % s;
+        const double *row = jack + j;
+        const int64_t step = (int64_t)JK_FIELDS * s;
+        double e;
+        if (f < 3) e = jack_se(B, [&](int b) { return row[b * step + (int64_t)f * s]; });
+        else if (f == 3) e = jack_se(B, [&](int b) { return 0.5 * (row[b * step] + row[b * step + s]); });
+        else e = P.free_ens ? jack_se(B, [&](int b) { return row[b * step] - jt[b * JK_TURN]; }) : NAN;
+        OUT(se[f], j) = e;
     }
 #undef OUT
 }
 
-// ---------------------------------------------------------------------------
-// The paper's sigma_i (Sec. IV A: gamma_i^2 = k sigma_i^2 / kT with sigma_i by
-// least-squares fitting of the x_i distribution): the Gaussian A exp(-(x -
-// mu)^2 / (2 sigma^2)) closest in least squares to the histogram density
-// count_b / (n dxi) at the bin centres, by Levenberg-Marquardt from the sample
-// moments.  One workgroup per window; each iteration sums J^T J, J^T r and the
-// squared residual over the bins in one block reduction.
-template <int NV>
-__device__ __forceinline__ void block_sum_vec(double (&v)[NV], double *sh) {
-    for (int q = 0; q < NV; ++q)
-        for (int off = 32; off >= 1; off >>= 1) v[q] += __shfl_xor(v[q], off);
-    const int wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0)
-        for (int q = 0; q < NV; ++q) sh[q * 4 + wave] = v[q];
-    __syncthreads();
-    for (int q = 0; q < NV; ++q) {
-        double t = 0;
-        for (int u = 0; u < n_waves; ++u) t += sh[q * 4 + u];
-        v[q] = t;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_gauss_fit(const DevProblem *__restrict__ probs, char *__restrict__ ws) {
-    const DevProblem &P = probs[blockIdx.y];
-    const int w = blockIdx.x, s = P.n_windows, K = P.xi_nbins;
-    if (w >= s) return;
-    double *out = dptr(ws, P.off_out);
-    const double *a = dptr(ws, P.off_tot) + (int64_t)w * A_NFIELDS;
-    const unsigned long long *hist = reinterpret_cast<const unsigned long long *>(ws + P.off_hist) + (int64_t)w * K;
-    const double *lam = dptr(ws, P.off_lambda);
-    __shared__ double sh[10 * 4];
-    __shared__ double s_p[3];
-    __shared__ int s_done;
-    const double n = a[A_N];
-    const double m1 = a[A_S1] / n;
-    const double var = (a[A_S2] - n * m1 * m1) / (n - 1.0);
-    double nz[1] = {0.0};                             // non-empty bins
-    for (int b = threadIdx.x; b < K; b += blockDim.x) nz[0] += hist[b] ? 1.0 : 0.0;
-    block_sum_vec<1>(nz, sh);
-    if (!(n > 2.0) || !(var > 0.0) || nz[0] < 3.0) {   // three parameters need three points
-        if (threadIdx.x == 0) { out[(int64_t)O_SIGMA_LSQ * s + w] = NAN; out[(int64_t)O_GAMMA2_LSQ * s + w] = NAN; }
-        return;
-    }
-    const double norm = 1.0 / (n * P.xi_bin);
-    double A = 1.0 / (sqrt(var) * 2.5066282746310002), mu = lam[w] + m1, sg = sqrt(var);
-    double lm = 1e-3;
-    // squared residual of (A, mu, sg)
-    auto cost = [&](double pA, double pm, double ps) {
-        double c[1] = {0.0};
-        const double i2 = 1.0 / (2.0 * ps * ps);
-        for (int b = threadIdx.x; b < K; b += blockDim.x) {
-            const double x = P.xi_min + ((double)b + 0.5) * P.xi_bin, d = x - pm;
-            const double r = (double)hist[b] * norm - pA * exp(-d * d * i2);
-            c[0] += r * r;
-        }
-        block_sum_vec<1>(c, sh);
-        return c[0];
-    };
-    double c0 = cost(A, mu, sg);
-    for (int it = 0; it < 200; ++it) {
-        double v[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};   // JtJ (6), Jtr (3), unused
-        const double i2 = 1.0 / (2.0 * sg * sg), is2 = 1.0 / (sg * sg);
-        for (int b = threadIdx.x; b < K; b += blockDim.x) {
-            const double x = P.xi_min + ((double)b + 0.5) * P.xi_bin, d = x - mu;
-            const double e = exp(-d * d * i2);
-            const double f = A * e;
-            const double r = (double)hist[b] * norm - f;
-            const double jA = e, jm = f * d * is2, js = f * d * d * is2 / sg;
-            v[0] += jA * jA; v[1] += jA * jm; v[2] += jA * js;
-            v[3] += jm * jm; v[4] += jm * js; v[5] += js * js;
-            v[6] += jA * r; v[7] += jm * r; v[8] += js * r;
-        }
-        block_sum_vec<10>(v, sh);
-        if (threadIdx.x == 0) {
-            // (J^T J + lm diag) delta = J^T r, by Cramer's rule on the 3x3 system
-            const double a00 = v[0] * (1 + lm), a11 = v[3] * (1 + lm), a22 = v[5] * (1 + lm);
-            const double a01 = v[1], a02 = v[2], a12 = v[4];
-            const double det = a00 * (a11 * a22 - a12 * a12) - a01 * (a01 * a22 - a12 * a02) + a02 * (a01 * a12 - a11 * a02);
-            const double b0 = v[6], b1 = v[7], b2 = v[8];
-            const double d0 = (b0 * (a11 * a22 - a12 * a12) - a01 * (b1 * a22 - a12 * b2) + a02 * (b1 * a12 - a11 * b2)) / det;
-            const double d1 = (a00 * (b1 * a22 - a12 * b2) - b0 * (a01 * a22 - a12 * a02) + a02 * (a01 * b2 - b1 * a02)) / det;
-            const double d2 = (a00 * (a11 * b2 - b1 * a12) - a01 * (a01 * b2 - b1 * a02) + b0 * (a01 * a12 - a11 * a02)) / det;
-            s_p[0] = A + d0; s_p[1] = mu + d1; s_p[2] = sg + d2;
-            s_done = (fabs(d0) <= 1e-14 * fabs(A) && fabs(d1) <= 1e-14 * (fabs(mu) + sg) && fabs(d2) <= 1e-14 * sg) ? 1 : 0;
-        }
-        __syncthreads();
-        const double nA = s_p[0], nm = s_p[1], ns = fabs(s_p[2]);
-        const int done = s_done;
-        const double c1 = cost(nA, nm, ns);
-        if (c1 <= c0) { A = nA; mu = nm; sg = ns; c0 = c1; lm = fmax(lm * 0.1, 1e-15); }
-        else lm *= 10.0;
-        if (done || lm > 1e12) break;
-    }
-    if (threadIdx.x == 0) {
-        out[(int64_t)O_SIGMA_LSQ * s + w] = sg;
-        out[(int64_t)O_GAMMA2_LSQ * s + w] = P.k * sg * sg / P.kT;
-    }
-}
-
-// Eq. 13 with gamma_i^2 from the fitted sigma_i, <x_i> the sample mean.
-__global__ void k_gauss_fit_profile(const DevProblem *__restrict__ probs, char *__restrict__ ws) {
-    const DevProblem &P = probs[blockIdx.x];
-    if (threadIdx.x != 0) return;
-    const int s = P.n_windows;
-    double *out = dptr(ws, P.off_out);
-    const double *lam = dptr(ws, P.off_lambda);
-    double g = 0.0;
-    out[(int64_t)O_DF_GAUSS_LSQ * s] = 0.0;
-    for (int j = 1; j < s; ++j) {
-        const double dl = lam[j] - lam[j - 1];
-        const double mean = out[(int64_t)O_XI_MEAN * s + j - 1];
-        const double g2 = out[(int64_t)O_GAMMA2_LSQ * s + j - 1];
-        g += P.k * dl * (lam[j - 1] - mean) + 0.5 * P.k * dl * dl * (1.0 - g2);
-        out[(int64_t)O_DF_GAUSS_LSQ * s + j] = g;
-    }
-}
-
 hipError_t launch_estimators(const DevProblem *d_probs, int n_probs, char *ws, int max_windows, hipStream_t stream) {
-    hipLaunchKernelGGL(k_estimators, dim3(n_probs), dim3(256), 0, stream, d_probs, ws);
-    hipLaunchKernelGGL(k_gauss_fit, dim3(max_windows, n_probs), dim3(256), 0, stream, d_probs, ws);
-    hipLaunchKernelGGL(k_gauss_fit_profile, dim3(n_probs), dim3(64), 0, stream, d_probs, ws);
+    hipLaunchKernelGGL(k_windows, dim3(max_windows, n_probs), dim3(256), 0, stream, d_probs, ws);
+    hipLaunchKernelGGL(k_profiles, dim3(n_probs), dim3(256), 0, stream, d_probs, ws);
     return hipGetLastError();
 }
 
