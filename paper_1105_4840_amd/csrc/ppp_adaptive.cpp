@@ -246,11 +246,10 @@ ppp_status ppp_adaptive_run(const ppp_problem *base, const ppp_adaptive *a, void
             hipMemcpy(mb.ys, ys.data(), nd * 4, hipMemcpyHostToDevice) != hipSuccess ||
             hipMemcpy(mb.ws, wsl.data(), nd * 4, hipMemcpyHostToDevice) != hipSuccess)
             return PPP_E_DEVICE;
-        for (int it = 0; it < a->train_iters; ++it) {
-            if (launch_mlp_grad(mb.params, mb.t, mb.yv, mb.wv, mb.ys, mb.ws, nd, mb.grad, mb.loss, st) != hipSuccess ||
-                launch_mlp_adam(mb.params, mb.grad, mb.m, mb.v, (float)a->lr, ++adam_step, st) != hipSuccess)
-                return PPP_E_DEVICE;
-        }
+        if (launch_mlp_train(mb.params, mb.t, mb.yv, mb.wv, mb.ys, mb.ws, nd, mb.m, mb.v, mb.loss, (float)a->lr,
+                             adam_step + 1, a->train_iters, st) != hipSuccess)
+            return PPP_E_DEVICE;
+        adam_step += a->train_iters;
         // ---- sigma(lambda) from the surrogate's curvature ----
         std::vector<float> gt(kGrid), gdy(kGrid);
         for (int i = 0; i < kGrid; ++i) gt[i] = (float)(-1.0 + 2.0 * i / (kGrid - 1));

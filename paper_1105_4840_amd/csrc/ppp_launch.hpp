@@ -38,6 +38,10 @@ hipError_t launch_appc(const DevProblem *d_probs, int n_probs, char *ws, int max
 hipError_t launch_mlp_forward(const float *params, const float *t, int n, float *y, float *dy, hipStream_t stream);
 hipError_t launch_mlp_grad(const float *params, const float *t, const float *yv, const float *wv, const float *ys,
                            const float *wsl, int n, float *grad, float *loss, hipStream_t stream);
+// `iters` steps of gradient and Adam from step number first_step on; loss: the last step's
+hipError_t launch_mlp_train(float *params, const float *t, const float *yv, const float *wv, const float *ys,
+                            const float *wsl, int n, float *m, float *v, float *loss, float lr, int first_step,
+                            int iters, hipStream_t stream);
 hipError_t launch_mlp_adam(float *params, const float *grad, float *m, float *v, float lr, int step,
                            hipStream_t stream);
 
