@@ -1,6 +1,7 @@
 """Builds libppp.so (HIP kernels for gfx950 + the C-ABI runtime) in-tree with hipcc."""
 import concurrent.futures
 import os
+import runpy
 import re
 import subprocess
 import sys
@@ -18,7 +19,7 @@ COMMON = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     # packed fp32 instructions are kept out of every kernel
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+    "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", os.path.join(OBJ, "gen"),
     "-Wall", "-Wno-unused-function", "-Wno-unknown-pragmas",
 ]
 
@@ -34,6 +35,10 @@ def _shape_sources():
     """One generated translation unit per (precision, shape) so they compile in parallel."""
     gen = os.path.join(OBJ, "gen")
     os.makedirs(gen, exist_ok=True)
+    header = os.path.join(gen, "ppp_lj_rounds.hpp")
+    text = runpy.run_path(os.path.join(HERE, "lj_rounds.py"))["header"]()
+    if not os.path.exists(header) or open(header).read() != text:
+        open(header, "w").write(text)
     out = []
     for g, b in shapes():
         for t in ("float", "double"):

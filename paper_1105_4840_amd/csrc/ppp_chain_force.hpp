@@ -5,12 +5,17 @@
 // (rcp_t, len_inv) and the noise (Normal6).
 #pragma once
 
+#if defined(__HIP_DEVICE_COMPILE__)
+#include "ppp_lj_rounds.hpp"
+#endif
+
 namespace ppp {
 
 // ===========================================================================
 // Chain model.
 // ===========================================================================
-template <typename T, int G, int B, bool ENERGY>
+// ASM: rounds 2 and on in assembly (the generated lj_rounds; device only).
+template <typename T, int G, int B, bool ENERGY, bool ASM = false>
 struct ChainForce {
     // groups of at most 6 lanes run no Newton-3 rounds beyond round 2
     static constexpr bool kHaloFromRound1 = G > 1 && (G - 1) / 2 <= 2;
@@ -25,7 +30,9 @@ struct ChainForce {
     // compiled for more waves per SIMD cannot spare.
     static constexpr bool kMaskFactors = G > 1 && G <= 6 && B == 2;
 
-    // Lennard-Jones between bead sets a (owned) and b; N3: also accumulate reaction on b.
+    // Lennard-Jones between bead sets a (owned) and b; N3: also accumulate the reaction
+    // on b in g (its opposite for the assembly's rounds, whose multiply-adds have no
+    // room for a sign).
     template <bool N3, bool MASK>
     __device__ __forceinline__ static void lj_block(const DevProblem &P, const T (&ax)[B], const T (&ay)[B],
                                                     const T (&az)[B], const T (&bx)[B], const T (&by)[B],
@@ -50,7 +57,8 @@ struct ChainForce {
                 f = ok ? f : (T)0;
                 if (ENERGY && ok) e_lj += (double)(ir6 * ((T)P.lj_eA * ir6 - (T)P.lj_eB)) - P.lj_ucut;
                 fx[b1] += f * dx; fy[b1] += f * dy; fz[b1] += f * dz;
-                if (N3) { gx[b2] -= f * dx; gy[b2] -= f * dy; gz[b2] -= f * dz; }
+                if (N3 && ASM) { gx[b2] += f * dx; gy[b2] += f * dy; gz[b2] += f * dz; }
+                else if (N3) { gx[b2] -= f * dx; gy[b2] -= f * dy; gz[b2] -= f * dz; }
             }
         }
     }
@@ -129,6 +137,12 @@ struct ChainForce {
                 }
             }
             // rounds 2 .. R_N3
+            if constexpr (ASM) {
+                static_assert(R_N3 >= 3 && B == 4 && sizeof(T) == 4 && !ENERGY, "the generated rounds");
+#if defined(__HIP_DEVICE_COMPILE__)
+                lj_rounds(R_N3 - 2, src, lA, lB, rc2, px, py, pz, qx, qy, qz, fx, fy, fz, gx, gy, gz);
+#endif
+            } else
 #pragma unroll 1
             for (int r = 2; r <= R_N3; ++r) {
                 pull_q();
@@ -143,7 +157,10 @@ struct ChainForce {
                 const int dst = solo ? me : gbase + ((g + G - R_N3) % G);
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
-                    fx[b] += push_f(dst, gx[b]); fy[b] += push_f(dst, gy[b]); fz[b] += push_f(dst, gz[b]);
+                    const T rx = push_f(dst, gx[b]), ry = push_f(dst, gy[b]), rz = push_f(dst, gz[b]);
+                    fx[b] = ASM ? fx[b] - rx : fx[b] + rx;
+                    fy[b] = ASM ? fy[b] - ry : fy[b] + ry;
+                    fz[b] = ASM ? fz[b] - rz : fz[b] + rz;
                 }
             }
             if constexpr (HALF && G > 2) {
@@ -293,7 +310,7 @@ __device__ __forceinline__ void lane_noise(const DevProblem &P, uint32_t gid, ui
 // forces at the new positions with the restraint centred at `centre`, and
 // v += dt/2 F/m.  Bead 0 (held fixed) and padding beads do not move.  f holds
 // the forces of the current positions on entry and of the new ones on return.
-template <typename T, int G, int B>
+template <typename T, int G, int B, bool ASM = false>
 __device__ __forceinline__ void baoab_step(const DevProblem &P, int g, int gbase, uint32_t gid, uint32_t n, T centre,
                                            T kr, T h, T hm, T c1, T c2sd, T (&px)[B], T (&py)[B], T (&pz)[B],
                                            T (&vx)[B], T (&vy)[B], T (&vz)[B], T (&fx)[B], T (&fy)[B], T (&fz)[B]) {
@@ -308,7 +325,7 @@ __device__ __forceinline__ void baoab_step(const DevProblem &P, int g, int gbase
             px[b] += h * vx[b]; py[b] += h * vy[b]; pz[b] += h * vz[b];
         }
     });
-    ChainForce<T, G, B, false>::compute(P, g, gbase, centre, kr, px, py, pz, fx, fy, fz, nullptr);
+    ChainForce<T, G, B, false, ASM>::compute(P, g, gbase, centre, kr, px, py, pz, fx, fy, fz, nullptr);
     if constexpr (ChainForce<T, G, B, false>::kMaskFactors) {
         // the closing half-kick with a zero factor for the fixed bead and the
         // padding (no select; the mobile beads' kick is the same FMA)

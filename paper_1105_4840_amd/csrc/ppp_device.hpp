@@ -208,15 +208,17 @@ __device__ __forceinline__ void lse_merge(double &m, double &S, double m2, doubl
 // exponential: the running maximum of 2a is twice that of a, so its rescaling
 // factor is the square of a's.  t = exp(-|a - m|) serves both branches, so
 // lanes that disagree on a > m still evaluate one exponential.
-__device__ __forceinline__ void lse_push_pair(double &m, double &S, double &m2, double &S2, double a) {
-    const double d = a - m;
-    const bool up = d > 0.0;
-    const double t = exp(up ? -d : d);
+__device__ __forceinline__ void lse_fold(double &m, double &S, double &m2, double &S2, double a, bool up, double t) {
     const double t2 = t * t;
     S = up ? S * t + 1.0 : S + t;
     S2 = up ? S2 * t2 + 1.0 : S2 + t2;
     m = up ? a : m;
     m2 = 2.0 * m;
+}
+__device__ __forceinline__ void lse_push_pair(double &m, double &S, double &m2, double &S2, double a) {
+    const double d = a - m;
+    const bool up = d > 0.0;
+    lse_fold(m, S, m2, S2, a, up, exp(up ? -d : d));
 }
 __device__ __forceinline__ double lse_value(double m, double S) {
     return S > 0.0 ? m + log(S) : -INFINITY;

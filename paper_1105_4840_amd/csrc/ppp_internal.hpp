@@ -111,5 +111,7 @@ constexpr int WG = 256;  // threads per workgroup of the simulation kernels
 // wavefront holds 64 / G whole groups and its last 64 mod G lanes stay idle.
 constexpr int groups_per_wave(int G) { return 64 / G; }
 constexpr int chain_reps_per_wg(int G) { return (WG / 64) * groups_per_wave(G); }
+// fp32 shapes with the Lennard-Jones rounds in assembly
+constexpr bool chain_asm_rounds(int G, int B) { return B == 4 && G >= 8; }
 
 }  // namespace ppp

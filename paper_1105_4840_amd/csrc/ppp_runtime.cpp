@@ -55,6 +55,7 @@ struct ppp_handle {
     std::vector<DevProblem> dev;     // the problems' device records, built with the layout
     std::vector<WorkItem> items;
     std::vector<VariantGroup> groups;
+    double items_cost = 0.0, longest_item = 0.0;   // pair-steps of all items and of the longest (batch)
     bool batch = false;
     int64_t off_probs = 0, off_items = 0, off_tickets = 0;
     int64_t ws_bytes = 0;
@@ -453,14 +454,33 @@ ppp_status mark(ppp_handle *h, int i, hipStream_t st) {
         if (m_ != PPP_OK) return m_;                     \
     } while (0)
 
+int device_cus() {
+    int cus = 256, dev = 0;
+    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    return cus;
+}
+
+// Whether a direct launch of `items` workgroups of the 64x4 shape takes the kernel
+// with the rounds in assembly.  It gains with three wavefronts a SIMD, one workgroup a
+// SIMD each; the compiled one runs two at most and is the better one at two.  256
+// beads, compiled / assembly by workgroups per CU: 1: 1.52 / 1.50 ms; 2: 2.07 / 2.16;
+// 3: 3.26 / 3.05; 4: 4.01 / 4.01; 8: 7.76 / 7.32; 24: 22.6 / 21.0.  A histogram that
+// keeps three workgroups from sharing a CU's 160 KB leaves it at two.
+bool third_wave_pays(int items, int lds_cap) {
+    const int cus = device_cus();
+    const int per_cu = (items + cus - 1) / cus;
+    return per_cu < 2 || (per_cu > 2 && lds_cap * 4 <= 48 * 1024);
+}
+
 ppp_status launch_items(ppp_handle *h, const ProblemHost &ph, int64_t b, int64_t e, hipStream_t st, double *traj,
                         int64_t traj_rep, int first, int count) {
     const int64_t nk = (int64_t)ph.item_windows * ph.dev.xi_nbins;
     const int cap = nk <= kLdsHistCap ? (int)nk : 0;
     const int G = ph.dev.model == PPP_MODEL_CHAIN ? ph.G : ph.lanes_1d;
+    const bool wide = ph.dev.model == PPP_MODEL_CHAIN && G == 64 && third_wave_pays(count, cap);
     if (!ph.dev.sequential) {
         HIPCHK(h, launch_sim(d_probs(h), d_items(h) + first, count, h->ws, b, e, ph.dev.model, ph.dev.precision, G,
-                             ph.B, traj, traj_rep, cap, st));
+                             ph.B, traj, traj_rep, cap, wide, st));
         return PPP_OK;
     }
     // sequential protocol: one launch per window touched, so a launch never
@@ -470,7 +490,7 @@ ppp_status launch_items(ppp_handle *h, const ProblemHost &ph, int64_t b, int64_t
     do {
         const int64_t stop = std::min(e, (at / T + 1) * T);
         HIPCHK(h, launch_sim(d_probs(h), d_items(h) + first, count, h->ws, at, stop, ph.dev.model, ph.dev.precision,
-                             G, ph.B, traj, traj_rep, cap, st));
+                             G, ph.B, traj, traj_rep, cap, wide, st));
         at = stop;
     } while (at < e);
     return PPP_OK;
@@ -717,7 +737,11 @@ ppp_status ppp_batch_create(const ppp_problem *ps, int32_t n, const char *tune_t
             for (auto &it : tmp) its.push_back({npair * it.n_reps * (double)ph.dev.n_steps, it});
         }
         std::stable_sort(its.begin(), its.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
-        for (auto &x : its) h->items.push_back(x.second);
+        for (auto &x : its) {
+            h->items.push_back(x.second);
+            h->items_cost += x.first;
+            h->longest_item = std::max(h->longest_item, x.first);
+        }
         g.n_items = (int)h->items.size() - g.first_item;
         h->groups.push_back(g);
     }
@@ -768,9 +792,14 @@ static ppp_status batch_capture(ppp_handle *h) {
         HIPCHK(h, hipEventCreateWithFlags(&e, hipEventDisableTiming));
         h->side_ev.push_back(e);
     }
-    int cus = 0, dev = 0;
-    HIPCHK(h, hipGetDevice(&dev));
-    HIPCHK(h, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int cus = device_cus();
+    // Three wavefronts a SIMD for the shapes with the rounds in assembly, or two: three
+    // is right where the batch is bound by throughput, wrong where it waits for its
+    // longest items, which then share their SIMD with two others instead of one.
+    // Measured on ten mixes of 2 to 12 chains of 8 to 128 beads, time at two / at three
+    // by total work / (the longest item's on every one of 3 workgroups per CU): 0.92 at
+    // 0.37, 0.90 at 0.95, 1.00 at 1.1 to 1.4, 1.06 at 1.9, 1.05 to 1.11 beyond.
+    const bool wide = h->items_cost >= 1.5 * 3.0 * cus * h->longest_item;
     HIPCHK(h, hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
     int *tickets = reinterpret_cast<int *>(h->ws + h->off_tickets);
     hipError_t e = launch_init(d_probs(h), (int)h->probs.size(), h->ws, h->max_windows, h->max_k, h->max_m, tickets, 64, h->cap);
@@ -783,9 +812,9 @@ static ppp_status batch_capture(ppp_handle *h) {
         for (auto &ph : h->probs)
             if (ph.dev.precision == g.precision && ph.G == g.G && ph.B == g.B) kmax = std::max(kmax, ph.dev.xi_nbins);
         const int cap = kmax <= kLdsHistCap ? kmax : 0;
-        const int per_cu = std::max(1, sim_blocks_per_cu(g.precision, g.G, g.B, cap));
+        const int per_cu = std::max(1, sim_blocks_per_cu(g.precision, g.G, g.B, cap, wide));
         const int groups = std::min(g.n_items, std::max(1, per_cu * cus));
-        if (e == hipSuccess) e = launch_sim_persistent(d_probs(h), d_items(h) + g.first_item, g.n_items, tickets + gi, h->ws, g.precision, g.G, g.B, groups, cap, h->side[gi]);
+        if (e == hipSuccess) e = launch_sim_persistent(d_probs(h), d_items(h) + g.first_item, g.n_items, tickets + gi, h->ws, g.precision, g.G, g.B, groups, cap, wide, h->side[gi]);
         if (e == hipSuccess) e = hipEventRecord(h->side_ev[gi + 1], h->side[gi]);
         if (e == hipSuccess) e = hipStreamWaitEvent(h->cap, h->side_ev[gi + 1], 0);
     }
@@ -1003,8 +1032,7 @@ ppp_status ppp_autotune(const char *path, void *ws, size_t bytes, void *stream) 
         PPP_FOR_EACH_SHAPE_RT(PPP_LIST)
 #undef PPP_LIST
     };
-    int cus = 256, dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int cus = device_cus();
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return PPP_E_DEVICE;
     std::ostringstream table;

@@ -23,19 +23,19 @@ __global__ void philox_blocks(uint64_t seed, uint32_t c0, uint32_t c1, uint32_t 
 
 #define PPP_DECLARE(GG, BB)                                                                                         \
     extern template hipError_t launch_chain_direct<float, GG, BB>(const DevProblem *, const WorkItem *, int, char *, \
-                                                                  int64_t, int64_t, double *, int64_t, int, hipStream_t); \
+                                                                  int64_t, int64_t, double *, int64_t, int, bool, hipStream_t); \
     extern template hipError_t launch_chain_direct<double, GG, BB>(const DevProblem *, const WorkItem *, int, char *, \
-                                                                   int64_t, int64_t, double *, int64_t, int, hipStream_t); \
+                                                                   int64_t, int64_t, double *, int64_t, int, bool, hipStream_t); \
     extern template hipError_t launch_chain_persistent<float, GG, BB>(const DevProblem *, const WorkItem *, int, int *, \
-                                                                      char *, int, int, hipStream_t);              \
+                                                                      char *, int, int, bool, hipStream_t);              \
     extern template hipError_t launch_chain_persistent<double, GG, BB>(const DevProblem *, const WorkItem *, int, int *, \
-                                                                       char *, int, int, hipStream_t);             \
+                                                                       char *, int, int, bool, hipStream_t);             \
     extern template hipError_t launch_chain_eval<float, GG, BB>(const DevProblem *, const double *, int, double, double *, \
                                                                 double *, hipStream_t);                            \
     extern template hipError_t launch_chain_eval<double, GG, BB>(const DevProblem *, const double *, int, double, double *, \
                                                                  double *, hipStream_t);                           \
-    extern template int chain_blocks_per_cu<float, GG, BB>(int);                                                   \
-    extern template int chain_blocks_per_cu<double, GG, BB>(int);
+    extern template int chain_blocks_per_cu<float, GG, BB>(int, bool);                                                   \
+    extern template int chain_blocks_per_cu<double, GG, BB>(int, bool);
 PPP_FOR_EACH_SHAPE(PPP_DECLARE)
 #undef PPP_DECLARE
 
@@ -46,9 +46,9 @@ bool chain_shape_supported(int G, int B) {
     return false;
 }
 
-int sim_blocks_per_cu(int precision, int G, int B, int lds_cap) {
+int sim_blocks_per_cu(int precision, int G, int B, int lds_cap, bool wide) {
 #define PPP_OCC(GG, BB) \
-    if (G == GG && B == BB) return precision == 1 ? chain_blocks_per_cu<double, GG, BB>(lds_cap) : chain_blocks_per_cu<float, GG, BB>(lds_cap);
+    if (G == GG && B == BB) return precision == 1 ? chain_blocks_per_cu<double, GG, BB>(lds_cap, wide) : chain_blocks_per_cu<float, GG, BB>(lds_cap, wide);
     PPP_FOR_EACH_SHAPE(PPP_OCC)
 #undef PPP_OCC
     return 1;
@@ -56,7 +56,7 @@ int sim_blocks_per_cu(int precision, int G, int B, int lds_cap) {
 
 hipError_t launch_sim(const DevProblem *d_probs, const WorkItem *d_items, int n_items, char *ws, int64_t step_begin,
                       int64_t step_end, int model, int precision, int G, int B, double *traj, int64_t traj_rep,
-                      int lds_cap, hipStream_t stream) {
+                      int lds_cap, bool wide, hipStream_t stream) {
     if (n_items <= 0) return hipSuccess;
     if (model == 0) {
         const size_t sh = (size_t)lds_cap * 4;
@@ -72,20 +72,21 @@ hipError_t launch_sim(const DevProblem *d_probs, const WorkItem *d_items, int n_
     }
 #define PPP_LAUNCH(GG, BB)                                                                                              \
     if (G == GG && B == BB)                                                                                            \
-        return precision == 1 ? launch_chain_direct<double, GG, BB>(d_probs, d_items, n_items, ws, step_begin, step_end, traj, traj_rep, lds_cap, stream) \
-                              : launch_chain_direct<float, GG, BB>(d_probs, d_items, n_items, ws, step_begin, step_end, traj, traj_rep, lds_cap, stream);
+        return precision == 1 ? launch_chain_direct<double, GG, BB>(d_probs, d_items, n_items, ws, step_begin, step_end, traj, traj_rep, lds_cap, wide, stream) \
+                              : launch_chain_direct<float, GG, BB>(d_probs, d_items, n_items, ws, step_begin, step_end, traj, traj_rep, lds_cap, wide, stream);
     PPP_FOR_EACH_SHAPE(PPP_LAUNCH)
 #undef PPP_LAUNCH
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_sim_persistent(const DevProblem *d_probs, const WorkItem *d_items, int n_items, int *d_ticket,
-                                 char *ws, int precision, int G, int B, int n_groups, int lds_cap, hipStream_t stream) {
+                                 char *ws, int precision, int G, int B, int n_groups, int lds_cap, bool wide,
+                                 hipStream_t stream) {
     if (n_items <= 0) return hipSuccess;
 #define PPP_LAUNCH(GG, BB)                                                                                              \
     if (G == GG && B == BB)                                                                                            \
-        return precision == 1 ? launch_chain_persistent<double, GG, BB>(d_probs, d_items, n_items, d_ticket, ws, n_groups, lds_cap, stream) \
-                              : launch_chain_persistent<float, GG, BB>(d_probs, d_items, n_items, d_ticket, ws, n_groups, lds_cap, stream);
+        return precision == 1 ? launch_chain_persistent<double, GG, BB>(d_probs, d_items, n_items, d_ticket, ws, n_groups, lds_cap, wide, stream) \
+                              : launch_chain_persistent<float, GG, BB>(d_probs, d_items, n_items, d_ticket, ws, n_groups, lds_cap, wide, stream);
     PPP_FOR_EACH_SHAPE(PPP_LAUNCH)
 #undef PPP_LAUNCH
     return hipErrorInvalidValue;

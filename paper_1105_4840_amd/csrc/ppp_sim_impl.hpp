@@ -99,28 +99,91 @@ __device__ __forceinline__ SampleCoef sample_coef(const DevProblem &P, const dou
     return c;
 }
 
+// exp(-y0) and exp(-y1), y >= 0: 2^n e^r with n = -rint(y / ln 2), |r| <= ln 2 / 2,
+// the series of e^r to r^13 (the next term is 4e-18); within 0.66 units in the last
+// place (the library's exp: 0.86).
+#define PPP_EXP_SERIES                                                                                                  \
+    1.4426950408889634, -0.6931471805599453, -2.3190468138462996e-17 /* log2 e, -ln 2 high, low */,                    \
+    1.6059043836821613e-10, 2.08767569878681e-09, 2.505210838544172e-08, 2.755731922398589e-07, 2.7557319223985893e-06, \
+    2.48015873015873e-05, 1.984126984126984e-04, 1.3888888888888889e-03, 8.333333333333333e-03, 4.1666666666666664e-02, \
+    1.6666666666666666e-01
+template <typename Table>
+__device__ __forceinline__ void exp_neg2(const Table &tab, double y0, double y1, double &t0, double &t1) {
+    y0 = y0 > 800.0 ? 800.0 : y0;             // e^-800 is 0
+    y1 = y1 > 800.0 ? 800.0 : y1;
+    const double n0 = rint(-y0 * tab[0]), n1 = rint(-y1 * tab[0]);
+    const double h0 = fma(n0, tab[1], -y0), h1 = fma(n1, tab[1], -y1);       // exact
+    const double r0 = fma(n0, tab[2], h0), r1 = fma(n1, tab[2], h1);
+    const double l0 = fma(n0, tab[2], h0 - r0), l1 = fma(n1, tab[2], h1 - r1);
+    double p0 = tab[3], p1 = p0;
+#pragma unroll
+    for (int i = 4; i < 14; ++i) {
+        p0 = fma(p0, r0, tab[i]);
+        p1 = fma(p1, r1, tab[i]);
+    }
+    p0 = fma(fma(p0, r0, 0.5), r0 * r0, l0);
+    p1 = fma(fma(p1, r1, 0.5), r1 * r1, l1);
+    const double s0 = 1.0 + r0, s1 = 1.0 + r1;                               // what it drops goes to the tail
+    t0 = ldexp(s0 + (((1.0 - s0) + r0) + p0), (int)n0);
+    t1 = ldexp(s1 + (((1.0 - s1) + r1) + p1), (int)n1);
+}
+
+// Where a sample's exponentials come from.  EXP_SERIES holds the coefficients in
+// registers over the step loop, as the library's exp does (some 38 of them).  EXP_LDS
+// reads them from LDS where they are used, at an offset that the compiler cannot see
+// through, for the kernels whose registers decide how many wavefronts a SIMD holds
+// (scalar loads from memory instead cost the 16x4 kernel 1% where a SIMD has one
+// wavefront).  The two give the same bits.
+enum ExpFrom { EXP_LIBRARY, EXP_SERIES, EXP_LDS };
+constexpr int kExpTerms = 14;
+__constant__ double kExpSeries[kExpTerms] = {PPP_EXP_SERIES};
+template <ExpFrom E>
+__device__ __forceinline__ void exp_pair(const double *lds_tab, double y0, double y1, double &t0, double &t1) {
+    if constexpr (E == EXP_LDS) {
+        int at = 0;
+        asm volatile("" : "+v"(at));
+        exp_neg2(lds_tab + at, y0, y1, t0, t1);
+    } else {
+        constexpr double tab[kExpTerms] = {PPP_EXP_SERIES};
+        exp_neg2(tab, y0, y1, t0, t1);
+    }
+}
+
 // Folds one sample xi of window w into the replica's accumulator.  The
 // histogram count goes to the workgroup's LDS copy of window w's histogram
 // (lhist) when there is one, else straight to memory.
+template <ExpFrom E>
 __device__ __forceinline__ void accumulate(const DevProblem &P, const SampleCoef &C, int w, double xi,
-                                           double *acc, unsigned long long *hist, unsigned int *lhist) {
+                                           double *acc, unsigned long long *hist, unsigned int *lhist,
+                                           const double *lds_exp) {
     const double d = xi - C.lam_w;
     acc[A_N] += 1.0;
     acc[A_S1] += d;
     acc[A_S2] += d * d;
     acc[A_XMIN] = fmin(acc[A_XMIN], xi);
     acc[A_XMAX] = fmax(acc[A_XMAX], xi);
-    if (C.kind_f == 1) {
-        lse_push_pair(acc[A_MF], acc[A_SF], acc[A_MF2], acc[A_SF2], C.cf * (d - C.hf));
-    } else if (C.kind_f == 2) {
-        const double e = xi - C.ref_f;
-        lse_push_pair(acc[A_MF], acc[A_SF], acc[A_MF2], acc[A_SF2], C.qf * e * e);
-    }
-    if (C.kind_r == 1) {
-        lse_push_pair(acc[A_MR], acc[A_SR], acc[A_MR2], acc[A_SR2], C.cr * (d - C.hr));
-    } else if (C.kind_r == 2) {
-        const double e = xi - C.ref_r;
-        lse_push_pair(acc[A_MR], acc[A_SR], acc[A_MR2], acc[A_SR2], C.qr * e * e);
+    if constexpr (E != EXP_LIBRARY) {
+        const double ef = xi - C.ref_f, er = xi - C.ref_r;
+        const double af = C.kind_f == 1 ? C.cf * (d - C.hf) : C.qf * ef * ef;
+        const double ar = C.kind_r == 1 ? C.cr * (d - C.hr) : C.qr * er * er;
+        const double df = af - acc[A_MF], dr = ar - acc[A_MR];
+        double tf, tr;
+        exp_pair<E>(lds_exp, fabs(df), fabs(dr), tf, tr);
+        if (C.kind_f) lse_fold(acc[A_MF], acc[A_SF], acc[A_MF2], acc[A_SF2], af, df > 0.0, tf);
+        if (C.kind_r) lse_fold(acc[A_MR], acc[A_SR], acc[A_MR2], acc[A_SR2], ar, dr > 0.0, tr);
+    } else {
+        if (C.kind_f == 1) {
+            lse_push_pair(acc[A_MF], acc[A_SF], acc[A_MF2], acc[A_SF2], C.cf * (d - C.hf));
+        } else if (C.kind_f == 2) {
+            const double e = xi - C.ref_f;
+            lse_push_pair(acc[A_MF], acc[A_SF], acc[A_MF2], acc[A_SF2], C.qf * e * e);
+        }
+        if (C.kind_r == 1) {
+            lse_push_pair(acc[A_MR], acc[A_SR], acc[A_MR2], acc[A_SR2], C.cr * (d - C.hr));
+        } else if (C.kind_r == 2) {
+            const double e = xi - C.ref_r;
+            lse_push_pair(acc[A_MR], acc[A_SR], acc[A_MR2], acc[A_SR2], C.qr * e * e);
+        }
     }
     const double fb = floor((xi - P.xi_min) / P.xi_bin);
     if (fb < 0.0) acc[A_UNDER] += 1.0;
@@ -514,9 +577,29 @@ __global__ __launch_bounds__(WG) void sim_1d(const DevProblem *__restrict__ prob
 }
 
 
-template <typename T, int G, int B>
+// Shapes with the Lennard-Jones rounds in assembly (ASM): fp32, four beads a lane, two
+// rounds or more after the first.  Such a kernel fetches the exponentials' coefficients
+// and keeps the samples' in LDS: rounds and sampling together then fit the registers of
+// three waves per SIMD (64x4: 166 instead of 197), which is where the rounds gain most.
+// At two the groups of 8 to 32 lanes still gain or break even; 64x4 loses 5%, so it has
+// the compiled kernel as well.  All kernels of such a shape use the same series, so a
+// replica's record is the same whichever runs it.
+template <typename T, int G, int B> constexpr bool asm_shape() { return sizeof(T) == 4 && chain_asm_rounds(G, B); }
+template <typename T, int G, int B> constexpr bool asm_only() { return asm_shape<T, G, B>() && G < 64; }
+template <typename T, int G, int B> constexpr ExpFrom exp_here() { return asm_shape<T, G, B>() ? EXP_SERIES : EXP_LIBRARY; }
+
+// What a workgroup of a chain kernel keeps in LDS besides the histogram: its
+// replicas' records and, with ASM, their coefficients and those of exp.
+template <int G, bool ASM> struct ChainLds {
+    // 16-byte accesses, but for the ASM kernels, which they cost 8 registers
+    alignas(ASM ? 8 : 16) double acc[chain_reps_per_wg(G)][A_NFIELDS];
+    SampleCoef coef[ASM ? chain_reps_per_wg(G) : 1];
+    double exp[ASM ? kExpTerms : 1];
+};
+
+template <typename T, int G, int B, bool ASM, ExpFrom E>
 __device__ __forceinline__ void run_chain_item(const DevProblem &P, const WorkItem &item, char *ws, int64_t step_begin,
-                                               int64_t step_end, double *traj, int64_t traj_rep, double *s_acc,
+                                               int64_t step_end, double *traj, int64_t traj_rep, ChainLds<G, ASM> &lds,
                                                unsigned int *lhist) {
     constexpr int NPAD = G * B;
     constexpr int GPW = groups_per_wave(G);
@@ -545,14 +628,22 @@ __device__ __forceinline__ void run_chain_item(const DevProblem &P, const WorkIt
     double *acc_g = reinterpret_cast<double *>(ws + P.off_acc) + grec * A_NFIELDS;
     T *st = state_ptr<T>(ws, P) + gi * 6 * NPAD;
     const double lam_w = lam[w];
-    const SampleCoef coef = sample_coef(P, lam, w);
     const int64_t n_end = step_end < s0 + P.n_steps ? step_end : s0 + P.n_steps;
     auto centre = [&](int64_t n) { return stage == 0 ? centre_at(P, lam_w, n) : lam_w; };
     const T kr = (T)window_k(P, w);
     const int i0 = g * B;
     const int last = N - 1;
     const int owner = last / B;       // lane (within group) owning the pulled end
-    double *acc = s_acc + grp * A_NFIELDS;
+    double *acc = lds.acc[grp];
+    SampleCoef coef_here;
+    if constexpr (ASM) {
+        // every wavefront writes all of them, so none waits for another
+        if (E == EXP_LDS && lane < kExpTerms) lds.exp[lane] = kExpSeries[lane];
+        if (lane_used && g == owner) lds.coef[grp] = sample_coef(P, lam, w);
+    } else {
+        coef_here = sample_coef(P, lam, w);
+    }
+    const SampleCoef &coef = ASM ? lds.coef[ASM ? grp : 0] : coef_here;
 
     T px[B], py[B], pz[B], vx[B], vy[B], vz[B], fx[B], fy[B], fz[B];
     if (step_begin == 0) {
@@ -598,7 +689,7 @@ __device__ __forceinline__ void run_chain_item(const DevProblem &P, const WorkIt
     const uint64_t bal0 = __ballot(blown0 != 0);
     bool alive = active && ((bal0 >> gbase) & ((G == 64) ? ~0ull : ((1ull << G) - 1))) == 0ull;
 
-    ChainForce<T, G, B, false>::compute(P, g, gbase, (T)centre(step_begin), kr, px, py, pz, fx, fy, fz, nullptr);
+    ChainForce<T, G, B, false, ASM>::compute(P, g, gbase, (T)centre(step_begin), kr, px, py, pz, fx, fy, fz, nullptr);
 
     const T h = (T)(0.5 * P.dt);
     const T c1 = (T)P.c1;
@@ -607,7 +698,7 @@ __device__ __forceinline__ void run_chain_item(const DevProblem &P, const WorkIt
     int64_t n_sample = s0 + next_sample_after(P, step_begin - s0);
     for (int64_t n = step_begin + 1; n <= n_end; ++n) {
         if (!alive) break;
-        baoab_step<T, G, B>(P, g, gbase, gid, (uint32_t)n, (T)centre(n), kr, h, hm, c1, c2sd, px, py, pz, vx, vy, vz,
+        baoab_step<T, G, B, ASM>(P, g, gbase, gid, (uint32_t)n, (T)centre(n), kr, h, hm, c1, c2sd, px, py, pz, vx, vy, vz,
                             fx, fy, fz);
         if (record && n <= 100000) {
 #pragma unroll
@@ -639,7 +730,7 @@ __device__ __forceinline__ void run_chain_item(const DevProblem &P, const WorkIt
                 if (g == owner) acc[A_BLOWN] = 1.0;
                 alive = false;
             } else if (g == owner) {
-                accumulate(P, coef, w, xi, acc, hist, lhist_w);
+                accumulate<E>(P, coef, w, xi, acc, hist, lhist_w, lds.exp);
             }
         }
     }
@@ -658,29 +749,28 @@ __device__ __forceinline__ void run_chain_item(const DevProblem &P, const WorkIt
 // round in flight (about 250 registers): it runs two waves per SIMD whatever
 // the schedule, and asked for more the scheduler trades that overlap away and
 // the kernel slows by a sixth.  Every other shape keeps the default (8).
-template <int G, int B> constexpr int chain_max_waves() { return (G == 64 && B == 4) ? 2 : 8; }
+template <int G, int B, bool ASM> constexpr int chain_max_waves() { return (G == 64 && B == 4 && !ASM) ? 2 : 8; }
 
 // Least waves per SIMD a direct launch is compiled for.  Left to itself the
 // compiler lands the fp32 kernels of chains longer than ten beads a few
-// registers above a wave boundary (16x2: 147 VGPRs, three waves; 3x4, 4x4 and
-// 8x4..32x4: 171-173, two waves).  Asked for one wave more they fit under it
-// (128, 168) without spilling and run 5-11% faster on 12- to 128-bead chains,
-// with the same machine arithmetic.  The 5x2 kernel keeps the default: the
-// 10-bead workload gives each SIMD fewer than two waves, and the tighter
-// budget costs it 4%.  The persistent kernel keeps one: its item loop holds
-// the fp64 exponential's constants in registers for the whole launch, and at
-// these floors it spills.
-template <typename T, int G, int B> constexpr int chain_min_waves() {
-    return sizeof(T) != 4 ? 1 : (B == 2 && G >= 8) ? 4 : (B == 4 && G >= 3 && G <= 32) ? 3 : 1;
+// registers above a wave boundary (16x2: 147 VGPRs, three waves; 3x4, 4x4:
+// 171-173, two waves).  Asked for one wave more they fit under it (128, 168)
+// without spilling and run 5-11% faster, with the same machine arithmetic.  The
+// 5x2 kernel keeps the default: the 10-bead workload gives each SIMD fewer than
+// two waves, and the tighter budget costs it 4%.  The persistent kernel keeps
+// one: its item loop holds the fp64 exponential's constants in registers for the
+// whole launch, and at these floors it spills.
+template <typename T, int G, int B, bool ASM> constexpr int chain_min_waves() {
+    return sizeof(T) != 4 ? 1 : (B == 2 && G >= 8) ? 4 : (ASM || (B == 4 && G >= 3 && G <= 32)) ? 3 : 1;
 }
 
 // Direct launch: one work item per workgroup.
-template <typename T, int G, int B>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(chain_min_waves<T, G, B>(), chain_max_waves<G, B>()))) void sim_chain(const DevProblem *__restrict__ probs, const WorkItem *__restrict__ items,
+template <typename T, int G, int B, bool ASM>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(chain_min_waves<T, G, B, ASM>(), chain_max_waves<G, B, ASM>()))) void sim_chain(const DevProblem *__restrict__ probs, const WorkItem *__restrict__ items,
                                                 int n_items, char *__restrict__ ws, int64_t step_begin,
                                                 int64_t step_end, double *__restrict__ traj, int64_t traj_rep,
                                                 int lds_cap) {
-    __shared__ double s_acc[chain_reps_per_wg(G) * A_NFIELDS];
+    __shared__ ChainLds<G, ASM> lds;
     extern __shared__ unsigned int s_hist[];
     if ((int)blockIdx.x >= n_items) return;
     const WorkItem item = items[blockIdx.x];
@@ -688,19 +778,19 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(chain_min_wa
     const int nk = item_hist_bins(P, item);
     unsigned int *lhist = nk <= lds_cap ? s_hist : nullptr;
     if (lhist) lhist_clear(lhist, nk);
-    run_chain_item<T, G, B>(P, item, ws, step_begin, step_end, traj, traj_rep, s_acc, lhist);
+    run_chain_item<T, G, B, ASM, ASM ? EXP_LDS : exp_here<T, G, B>()>(P, item, ws, step_begin, step_end, traj, traj_rep, lds, lhist);
     const int64_t w0 = P.sequential ? seq_window(P, step_begin) : item.window;
     if (lhist) lhist_flush(lhist, nk, reinterpret_cast<unsigned long long *>(ws + P.off_hist) + w0 * P.xi_nbins);
 }
 
 // Persistent launch: workgroups take items from a queue (atomic ticket) until
 // it is empty; items are ordered longest first by the host.
-template <typename T, int G, int B>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(1, chain_max_waves<G, B>()))) void sim_chain_persistent(const DevProblem *__restrict__ probs,
+template <typename T, int G, int B, bool ASM, ExpFrom E>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(1, chain_max_waves<G, B, ASM>()))) void sim_chain_persistent(const DevProblem *__restrict__ probs,
                                                            const WorkItem *__restrict__ items, int n_items,
                                                            int *__restrict__ ticket, char *__restrict__ ws,
                                                            int lds_cap) {
-    __shared__ double s_acc[chain_reps_per_wg(G) * A_NFIELDS];
+    __shared__ ChainLds<G, ASM> lds;
     __shared__ int s_item;
     extern __shared__ unsigned int s_hist[];
     for (;;) {
@@ -714,7 +804,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(1, chain_max
         const int nk = item_hist_bins(P, item);
         unsigned int *lhist = nk <= lds_cap ? s_hist : nullptr;
         if (lhist) lhist_clear(lhist, nk);
-        run_chain_item<T, G, B>(P, item, ws, 0, INT64_MAX, nullptr, -1, s_acc, lhist);
+        run_chain_item<T, G, B, ASM, E>(P, item, ws, 0, INT64_MAX, nullptr, -1, lds, lhist);
         if (lhist) lhist_flush(lhist, nk, reinterpret_cast<unsigned long long *>(ws + P.off_hist) + (int64_t)item.window * P.xi_nbins);
     }
 }
@@ -784,19 +874,28 @@ __global__ void pot1d_eval(const DevProblem *__restrict__ probs, const double *_
 }
 
 // Per-shape launchers; each shape is instantiated in its own translation unit.
+// wide: enough work for three waves per SIMD.
+template <typename T, int G, int B> auto direct_kernel(bool wide) {
+    return wide ? sim_chain<T, G, B, asm_shape<T, G, B>()> : sim_chain<T, G, B, asm_only<T, G, B>()>;
+}
+template <typename T, int G, int B> auto persistent_kernel(bool wide) {
+    constexpr bool ASM = asm_shape<T, G, B>(), ONLY = asm_only<T, G, B>();
+    return wide ? sim_chain_persistent<T, G, B, ASM, ASM ? EXP_LDS : EXP_LIBRARY>
+                : sim_chain_persistent<T, G, B, ONLY, exp_here<T, G, B>()>;    // 190 registers and more: two waves
+}
 template <typename T, int G, int B>
 hipError_t launch_chain_direct(const DevProblem *d_probs, const WorkItem *d_items, int n_items, char *ws,
                                int64_t step_begin, int64_t step_end, double *traj, int64_t traj_rep, int lds_cap,
-                               hipStream_t stream) {
-    hipLaunchKernelGGL((sim_chain<T, G, B>), dim3(n_items), dim3(WG), (size_t)lds_cap * 4, stream, d_probs, d_items,
+                               bool wide, hipStream_t stream) {
+    hipLaunchKernelGGL((direct_kernel<T, G, B>(wide)), dim3(n_items), dim3(WG), (size_t)lds_cap * 4, stream, d_probs, d_items,
                        n_items, ws, step_begin, step_end, traj, traj_rep, lds_cap);
     return hipGetLastError();
 }
 template <typename T, int G, int B>
 hipError_t launch_chain_persistent(const DevProblem *d_probs, const WorkItem *d_items, int n_items, int *d_ticket,
-                                   char *ws, int n_groups, int lds_cap, hipStream_t stream) {
-    hipLaunchKernelGGL((sim_chain_persistent<T, G, B>), dim3(n_groups), dim3(WG), (size_t)lds_cap * 4, stream, d_probs,
-                       d_items, n_items, d_ticket, ws, lds_cap);
+                                   char *ws, int n_groups, int lds_cap, bool wide, hipStream_t stream) {
+    hipLaunchKernelGGL((persistent_kernel<T, G, B>(wide)), dim3(n_groups), dim3(WG), (size_t)lds_cap * 4, stream,
+                       d_probs, d_items, n_items, d_ticket, ws, lds_cap);
     return hipGetLastError();
 }
 template <typename T, int G, int B>
@@ -809,19 +908,19 @@ hipError_t launch_chain_eval(const DevProblem *d_probs, const double *coords, in
     return hipGetLastError();
 }
 template <typename T, int G, int B>
-int chain_blocks_per_cu(int lds_cap) {
+int chain_blocks_per_cu(int lds_cap, bool wide) {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sim_chain_persistent<T, G, B>, WG, (size_t)lds_cap * 4) != hipSuccess) n = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, persistent_kernel<T, G, B>(wide), WG, (size_t)lds_cap * 4) != hipSuccess) n = 1;
     return n;
 }
 
 #define PPP_INSTANTIATE_SHAPE(T, G, B)                                                                              \
     template hipError_t launch_chain_direct<T, G, B>(const DevProblem *, const WorkItem *, int, char *, int64_t,   \
-                                                     int64_t, double *, int64_t, int, hipStream_t);                \
+                                                     int64_t, double *, int64_t, int, bool, hipStream_t);          \
     template hipError_t launch_chain_persistent<T, G, B>(const DevProblem *, const WorkItem *, int, int *, char *, \
-                                                         int, int, hipStream_t);                                   \
+                                                         int, int, bool, hipStream_t);                             \
     template hipError_t launch_chain_eval<T, G, B>(const DevProblem *, const double *, int, double, double *,      \
                                                    double *, hipStream_t);                                         \
-    template int chain_blocks_per_cu<T, G, B>(int);
+    template int chain_blocks_per_cu<T, G, B>(int, bool);
 
 }  // namespace ppp
