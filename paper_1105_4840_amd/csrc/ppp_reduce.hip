@@ -639,8 +639,9 @@ hipError_t launch_estimators(const DevProblem *d_probs, int n_probs, char *ws, i
 // rho_{i+1} with the work of moving the centre back, dW^rev_i(x) = k/2
 // [(x - lambda_i)^2 - (x - lambda_{i+1})^2], x at the bin centre, move floor.
 //
-// One 256-thread block per (window step, problem, chain).  The bins are taken 256
-// at a time: the non-empty ones are compacted in order, run heads are marked, and
+// One 256-thread block per (window step, problem, chain), bound by the block scans' barriers:
+// some 2 us for 256 bins, so the bins outside the window's samples are left out (50000
+// bins, most of them empty: 390 -> 22 us).  The bins are taken 256 at a time: the non-empty ones are compacted in order, run heads are marked, and
 // each head sums its run left to right, the first run of a chunk continuing the
 // last one of the previous chunk where the shifts agree, so every probability is
 // the same left-to-right sum as in a sequential pass.
@@ -683,10 +684,16 @@ __global__ __launch_bounds__(256) void k_appc_pairs(const DevProblem *__restrict
     __shared__ int s_scan[256];
     __shared__ int s_k0[256], s_k1[256], s_head[256];
     __shared__ double s_pb[256];
+    // the bins between the window's smallest and largest sample, and one on either side
+    const double *rec = tot + (int64_t)src * A_NFIELDS;
+    const double d_lo = floor((rec[A_XMIN] - P.xi_min) / P.xi_bin) - 1.0;
+    const double d_hi = floor((rec[A_XMAX] - P.xi_min) / P.xi_bin) + 1.0;
+    const int b_lo = d_lo < 0.0 ? 0 : (d_lo < (double)K ? (int)d_lo : K);
+    const int b_hi = d_hi < 0.0 ? -1 : (d_hi < (double)K ? (int)d_hi : K - 1);
     int np = 0, last0 = 0, last1 = 0;
-    for (int c0 = 0; c0 < K; c0 += 256) {
+    for (int c0 = b_lo; c0 <= b_hi; c0 += 256) {
         const int b = c0 + t;
-        const unsigned long long c = b < K ? hist[b] : 0ull;
+        const unsigned long long c = b <= b_hi ? hist[b] : 0ull;
         int k0 = 0, k1 = 0;
         double pb = 0.0;
         if (c != 0ull) {
@@ -848,7 +855,12 @@ __global__ __launch_bounds__(256) void k_appc_step(const DevProblem *__restrict_
 }
 
 // Statistics of Omega_j: normalised exponential average (App. B.5), spread and
-// the number of non-empty bins, the JE variance formula of Sec. IV A.
+// the number of non-empty bins, the JE variance formula of Sec. IV A.  One block per
+// (window, problem, chain), bound by the latency of its passes over the bins, so a thread
+// has eight loads in flight; it adds in bin order all the same (1 - the sum is an output
+// of rounding size).  One load at a time: 131 us over 30001 bins, 297 over 90001; so:
+// 71 and 135 us.
+constexpr int kAppcAhead = 8;
 __global__ __launch_bounds__(256) void k_appc_stats(const DevProblem *__restrict__ probs, char *__restrict__ ws) {
     const DevProblem &P = probs[blockIdx.y];
     const int j = blockIdx.x;
@@ -864,14 +876,24 @@ __global__ __launch_bounds__(256) void k_appc_stats(const DevProblem *__restrict
     const double shift_mid = 0.5 * (double)j * dWb;
     double tot = 0, q = 0, mw = 0, emax = -INFINITY;
     const bool smooth = chain == 1 && j >= 1;   // chain 1 keeps W = 0 unsmoothed in memory
-    for (int64_t b = threadIdx.x; b < nb; b += blockDim.x) {
-        const double o = omega_at(om, b, M, smooth);
-        if (o != 0.0) {
-            const double W = (double)(b - M) * dWb;
-            tot += o; q += 1.0; mw += o * W;
-            emax = fmax(emax, -beta * W);
+    auto bins = [&](auto &&use) {               // use(b, Omega_j(b)) for the thread's non-empty bins, in order
+        for (int64_t b0 = threadIdx.x; b0 < nb; b0 += 256 * kAppcAhead) {
+            double o[kAppcAhead];
+#pragma unroll
+            for (int r = 0; r < kAppcAhead; ++r) o[r] = b0 + 256 * r < nb ? om[b0 + 256 * r] : 0.0;
+#pragma unroll
+            for (int r = 0; r < kAppcAhead; ++r) {
+                const int64_t b = b0 + 256 * r;
+                if (smooth && b == M) o[r] = omega_at(om, M, M, true);
+                if (o[r] != 0.0) use(b, o[r]);
+            }
         }
-    }
+    };
+    bins([&](int64_t b, double o) {
+        const double W = (double)(b - M) * dWb;
+        tot += o; q += 1.0; mw += o * W;
+        emax = fmax(emax, -beta * W);
+    });
     tot = block_sum(tot, sh);
     q = block_sum(q, sh);
     mw = block_sum(mw, sh);
@@ -886,15 +908,12 @@ __global__ __launch_bounds__(256) void k_appc_stats(const DevProblem *__restrict
     __syncthreads();
     const double mean = mw / tot;
     double sl = 0, sm = 0, vv = 0;
-    for (int64_t b = threadIdx.x; b < nb; b += blockDim.x) {
-        const double o = omega_at(om, b, M, smooth);
-        if (o != 0.0) {
-            const double W = (double)(b - M) * dWb;
-            sl += o * exp(-beta * W - emax);
-            sm += o * exp(-beta * (W + shift_mid) - emax);
-            vv += o * (W - mean) * (W - mean);
-        }
-    }
+    bins([&](int64_t b, double o) {
+        const double W = (double)(b - M) * dWb;
+        sl += o * exp(-beta * W - emax);
+        sm += o * exp(-beta * (W + shift_mid) - emax);
+        vv += o * (W - mean) * (W - mean);
+    });
     sl = block_sum(sl, sh);
     sm = block_sum(sm, sh);
     vv = block_sum(vv, sh);
@@ -906,16 +925,24 @@ __global__ __launch_bounds__(256) void k_appc_stats(const DevProblem *__restrict
         // in [v, v + j) dW, so -W_rev matches forward bin w at v = -w - j.
         const double *of = dptr(ws, P.off_omega) + (int64_t)j * nb;      // chain 0
         double ovl = 0, wm = 0, wf = 0;
-        for (int64_t b = threadIdx.x; b < nb; b += blockDim.x) {
-            const int64_t v = 2 * (int64_t)M - b - j;                     // index of bin -w - j
-            if (v < 0 || v >= nb) continue;
-            const double f = of[b], r = om[v];
-            const double m = fmin(f, r);
-            ovl += m;
-            if (f > 0.0 && r > 0.0) {
-                // P_f(W) / P_r(-W) = exp(beta (W - dF)): each common bin gives W - kT ln(P_f / P_r)
-                wm += m;
-                wf += m * (((double)(b - M) + 0.5 * j) * dWb - P.kT * log(f / r));
+        for (int64_t b0 = threadIdx.x; b0 < nb; b0 += 256 * kAppcAhead) {
+            double f[kAppcAhead], r[kAppcAhead];
+#pragma unroll
+            for (int q8 = 0; q8 < kAppcAhead; ++q8) {
+                const int64_t b = b0 + 256 * q8, v = 2 * (int64_t)M - b - j;      // index of bin -w - j
+                const bool in = b < nb && v >= 0 && v < nb;
+                f[q8] = in ? of[b] : 0.0;
+                r[q8] = in ? om[v] : 0.0;
+            }
+#pragma unroll
+            for (int q8 = 0; q8 < kAppcAhead; ++q8) {
+                const double m = fmin(f[q8], r[q8]);
+                ovl += m;
+                if (f[q8] > 0.0 && r[q8] > 0.0) {
+                    // P_f(W) / P_r(-W) = exp(beta (W - dF)): each common bin gives W - kT ln(P_f / P_r)
+                    wm += m;
+                    wf += m * (((double)(b0 + 256 * q8 - M) + 0.5 * j) * dWb - P.kT * log(f[q8] / r[q8]));
+                }
             }
         }
         ovl = block_sum(ovl, sh);
