@@ -984,9 +984,8 @@ ppp_status ppp_eval_forces(ppp_handle *h, void *ws, size_t bytes, const double *
     if (s != PPP_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     h->ws = static_cast<char *>(ws);
-    if ((s = upload(h, st)) != PPP_OK) return s;
     const ProblemHost &ph = h->probs[0];
-    HIPCHK(h, launch_eval(d_probs(h), d_coords, n_rep, lambda, d_forces, d_energy, ph.dev.model, ph.dev.precision, ph.G, ph.B, st));
+    HIPCHK(h, launch_eval(h->dev[0], d_coords, n_rep, lambda, d_forces, d_energy, ph.dev.model, ph.dev.precision, ph.G, ph.B, st));
     h->begun = false; h->finalized = false;
     return PPP_OK;
 }

@@ -30,9 +30,9 @@ __global__ void philox_blocks(uint64_t seed, uint32_t c0, uint32_t c1, uint32_t 
                                                                       char *, int, int, bool, hipStream_t);              \
     extern template hipError_t launch_chain_persistent<double, GG, BB>(const DevProblem *, const WorkItem *, int, int *, \
                                                                        char *, int, int, bool, hipStream_t);             \
-    extern template hipError_t launch_chain_eval<float, GG, BB>(const DevProblem *, const double *, int, double, double *, \
+    extern template hipError_t launch_chain_eval<float, GG, BB>(const DevProblem &, const double *, int, double, double *, \
                                                                 double *, hipStream_t);                            \
-    extern template hipError_t launch_chain_eval<double, GG, BB>(const DevProblem *, const double *, int, double, double *, \
+    extern template hipError_t launch_chain_eval<double, GG, BB>(const DevProblem &, const double *, int, double, double *, \
                                                                  double *, hipStream_t);                           \
     extern template int chain_blocks_per_cu<float, GG, BB>(int, bool);                                                   \
     extern template int chain_blocks_per_cu<double, GG, BB>(int, bool);
@@ -92,19 +92,19 @@ hipError_t launch_sim_persistent(const DevProblem *d_probs, const WorkItem *d_it
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_eval(const DevProblem *d_probs, const double *coords, int n_rep, double centre, double *forces,
+hipError_t launch_eval(const DevProblem &prob, const double *coords, int n_rep, double centre, double *forces,
                        double *energy, int model, int precision, int G, int B, hipStream_t stream) {
     if (n_rep <= 0) return hipSuccess;
     if (model == 0) {
         const int nb = (n_rep + 255) / 256;
-        if (precision == 1) hipLaunchKernelGGL(pot1d_eval<double>, dim3(nb), dim3(256), 0, stream, d_probs, coords, n_rep, centre, forces, energy);
-        else hipLaunchKernelGGL(pot1d_eval<float>, dim3(nb), dim3(256), 0, stream, d_probs, coords, n_rep, centre, forces, energy);
+        if (precision == 1) hipLaunchKernelGGL(pot1d_eval<double>, dim3(nb), dim3(256), 0, stream, prob, coords, n_rep, centre, forces, energy);
+        else hipLaunchKernelGGL(pot1d_eval<float>, dim3(nb), dim3(256), 0, stream, prob, coords, n_rep, centre, forces, energy);
         return hipGetLastError();
     }
 #define PPP_LAUNCH(GG, BB)                                                                                              \
     if (G == GG && B == BB)                                                                                            \
-        return precision == 1 ? launch_chain_eval<double, GG, BB>(d_probs, coords, n_rep, centre, forces, energy, stream) \
-                              : launch_chain_eval<float, GG, BB>(d_probs, coords, n_rep, centre, forces, energy, stream);
+        return precision == 1 ? launch_chain_eval<double, GG, BB>(prob, coords, n_rep, centre, forces, energy, stream) \
+                              : launch_chain_eval<float, GG, BB>(prob, coords, n_rep, centre, forces, energy, stream);
     PPP_FOR_EACH_SHAPE(PPP_LAUNCH)
 #undef PPP_LAUNCH
     return hipErrorInvalidValue;
