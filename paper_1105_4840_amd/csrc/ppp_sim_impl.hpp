@@ -580,7 +580,7 @@ __global__ __launch_bounds__(WG) void sim_1d(const DevProblem *__restrict__ prob
 // Shapes with the Lennard-Jones rounds in assembly (ASM): fp32, four beads a lane, two
 // rounds or more after the first.  Such a kernel fetches the exponentials' coefficients
 // and keeps the samples' in LDS: rounds and sampling together then fit the registers of
-// three waves per SIMD (64x4: 166 instead of 197), which is where the rounds gain most.
+// three waves per SIMD (64x4: 165 instead of 197), which is where the rounds gain most.
 // At two the groups of 8 to 32 lanes still gain or break even; 64x4 loses 5%, so it has
 // the compiled kernel as well.  All kernels of such a shape use the same series, so a
 // replica's record is the same whichever runs it.
