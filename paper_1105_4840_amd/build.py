@@ -1,8 +1,8 @@
 """Builds libppp.so (HIP kernels for gfx950 + the C-ABI runtime) in-tree with hipcc."""
 import concurrent.futures
 import os
-import runpy
 import re
+import runpy
 import subprocess
 import sys
 
