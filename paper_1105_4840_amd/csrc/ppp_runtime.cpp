@@ -478,14 +478,11 @@ ppp_status launch_items(ppp_handle *h, const ProblemHost &ph, int64_t b, int64_t
     const int cap = nk <= kLdsHistCap ? (int)nk : 0;
     const int G = ph.dev.model == PPP_MODEL_CHAIN ? ph.G : ph.lanes_1d;
     const bool wide = ph.dev.model == PPP_MODEL_CHAIN && G == 64 && third_wave_pays(count, cap);
-    if (!ph.dev.sequential) {
-        HIPCHK(h, launch_sim(d_probs(h), d_items(h) + first, count, h->ws, b, e, ph.dev.model, ph.dev.precision, G,
-                             ph.B, traj, traj_rep, cap, wide, st));
-        return PPP_OK;
-    }
     // sequential protocol: one launch per window touched, so a launch never
-    // crosses a window boundary (the kernel takes the window from its first step)
-    const int64_t T = ph.dev.n_steps;
+    // crosses a window boundary (the kernel takes the window from its first step);
+    // parallel: no launch from step 0 to step 2^32 - 1 (the 1-D kernel's step numbers
+    // would have no value left for "no sample in this launch")
+    const int64_t T = ph.dev.sequential ? ph.dev.n_steps : (int64_t)1 << 31;
     int64_t at = b;
     do {
         const int64_t stop = std::min(e, (at / T + 1) * T);

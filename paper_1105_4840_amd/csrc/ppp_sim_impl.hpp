@@ -326,6 +326,16 @@ template <int N, typename Fn> __device__ __forceinline__ void static_for(Fn &&fn
     }
 }
 
+// First sampled step of a launch that ends with step n_end, n_end + 1 if it has none: the
+// next sampled step itself may lie beyond 2^32 (n_equil and sample_every are bounded by
+// 2^32 and 2^31 alone).  A launch from step 0 ends below 2^32 - 1 (launch_items), so
+// n_end + 1 is never step 0, which the first tile holds.  After a sample the number may
+// wrap, but only to less than the step just sampled, which no later step equals.
+__device__ __forceinline__ uint32_t first_sample_1d(const DevProblem &P, int64_t s0, int64_t step_begin, uint32_t n_end) {
+    const int64_t next = s0 + next_sample_after(P, step_begin - s0);
+    return next <= (int64_t)n_end ? (uint32_t)next : n_end + 1u;
+}
+
 template <typename T, int L, int POT>
 __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int rep, char *ws, int64_t step_begin,
                                                int64_t step_end, double *traj, int traj_rep, unsigned int *lhist,
@@ -409,7 +419,7 @@ __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int r
     }
 
     uint32_t n = (uint32_t)step_begin, drawn = 1u;   // drawn: the tile z belongs to (tiles start at multiples of 4)
-    uint32_t n_sample = (uint32_t)(s0 + next_sample_after(P, step_begin - s0));
+    uint32_t n_sample = first_sample_1d(P, s0, step_begin, n_end);
     T z[4];
     while (n < n_end && __any(alive)) {
         // the tile of step n + 1: kTile steps from `base`, block b of four steps with its normals in lane b
