@@ -165,9 +165,13 @@ __device__ __forceinline__ void block_sum_vec(double (&v)[NV], double *sh) {
 // Lane l holds blocks [l c, (l + 1) c), c = ceil(B / 64).  A log-sum-exp without
 // block b is taken against the largest maximum among the others: the overall
 // maximum M, or for the block that holds it the next one; its sum is the sum of
-// the blocks before plus that of the blocks after, so nothing cancels.  Every
-// block then costs one exponential a direction instead of the B - 1 merges that
-// each leave-one-out record took when it was built by itself.
+// the blocks before plus that of the blocks after, so nothing cancels in it.  Every
+// block then costs c exponentials a direction (one up to 64 blocks; its lane's
+// others are added again) instead of the B - 1 merges that each leave-one-out record
+// took when it was built by itself.  Counts (exact) and moments are the total less the
+// block: a moment is then off by rounding of the total, which matters only where one
+// block outweighs the others, and there the standard error is as large as that total.
+// 21 windows, 300 blocks: 0.8 ms for all estimators, 11.1 with merges; 4096: 3.0, 1890.
 // ---------------------------------------------------------------------------
 struct LseLoo {
     double m, s, s2;          // all blocks: maximum, scaled sum, scaled sum of squares (of 2a)
