@@ -203,23 +203,42 @@ void default_shape(int N, int precision, int &G, int &B) {
     else { G = 64; B = 4; }
 }
 
-// Lanes per replica of the 1-D kernel for a number of replicas (all windows).
+// Lanes per replica of the 1-D kernel for the replicas of all windows.
 // More lanes shorten a replica's own time (they share its noise and its
 // sampling exponentials) but every lane takes the steps, so they pay only while
 // SIMDs would idle: up to one wavefront per SIMD (65536 lanes), twice or three
 // times that where the next split is the coarse one.  MI355X, double well, 2000
 // steps, kernel ms in fp64 (fp32) at 1 / 2 / 4 / 8 / 16 lanes:
-//   2688 replicas  0.56 / 0.34 / 0.22 / 0.16 / 0.12 (0.35 / 0.22 / 0.16 / 0.12 / 0.09)
-//   5376           0.57 / 0.34 / 0.22 / 0.17 / 0.18 (0.35 / 0.22 / 0.16 / 0.12 / 0.13)
-//   8400           0.56 / 0.40 / 0.22 / 0.24 / 0.25 (0.35 / 0.24 / 0.16 / 0.16 / 0.19)
-//   43008          0.56 / 0.49 / 0.44 / 0.58 / 0.81 (0.35 / 0.28 / 0.27 / 0.38 / 0.58)
-//   86016          0.81 / 0.67 / 0.81 / 1.03 / 1.48 (0.43 / 0.36 / 0.48 / 0.68 / 1.06)
-//   172032         1.10 / 1.21 / 1.37 / 1.85 / 2.89 (0.53 / 0.66 / 0.83 / 1.24 / 2.08)
-int default_lanes_1d(int64_t replicas) {
+//   2688 replicas  0.49 / 0.33 / 0.21 / 0.16 / 0.12 (0.31 / 0.22 / 0.16 / 0.12 / 0.10)
+//   5376           0.48 / 0.33 / 0.21 / 0.16 / 0.18 (0.30 / 0.22 / 0.16 / 0.12 / 0.13)
+//   8400           0.49 / 0.40 / 0.22 / 0.23 / 0.25 (0.30 / 0.24 / 0.16 / 0.16 / 0.19)
+//   43008          0.49 / 0.49 / 0.43 / 0.62 / 0.83 (0.30 / 0.28 / 0.26 / 0.38 / 0.57)
+//   86016          0.74 / 0.65 / 0.76 / 0.99 / 1.45 (0.37 / 0.35 / 0.47 / 0.64 / 1.05)
+//   172032         1.02 / 1.19 / 1.34 / 1.84 / 2.87 (0.47 / 0.64 / 0.80 / 1.17 / 2.06)
+// Two lanes end where their workgroups pass three a CU: with 16384 bins in fp32, 600
+// steps, 0.139 / 0.234 at 94500 replicas, 0.140 / 0.296 at 105000 (0.268 either way
+// with a lane per replica and one step after another).
+//
+// A run whose steps are mostly taken one by one (a sample every one to three steps,
+// or a long pull) shares no more than the noise, and its lanes pay up to three
+// wavefronts a SIMD alone (a window's replicas fill whole wavefronts); beyond that
+// the split cost more than it gave.  fp32, 600 steps, a sample every third:
+//   43008 (21 windows)    0.252 / 0.296 / 0.280, a lane per replica and one step after another 0.297
+//   49140 (21)            0.252 / 0.301 / 0.399 (0.302)
+//   44850 (690)           0.328 / 0.354 / 0.518 (0.372)
+//   131061 (21)           0.382 / 0.580 / 0.733 (0.410)
+// fp64 with a sample every step, 86016: 0.83 / 0.76 / 0.88 (0.99).
+int default_lanes_1d(const ppp_problem &p, int64_t windows) {
+    const int64_t replicas = windows * p.n_replicas;
     if (replicas <= 4096) return 16;
     if (replicas <= 8192) return 8;
+    auto fits = [&](int lanes) { return windows * (((int64_t)p.n_replicas * lanes + 63) / 64) <= 3 * 1024; };
+    if (p.sample_every < 4 || p.n_pull > p.n_steps / 2) {
+        if (fits(4)) return 4;
+        return p.sample_every < 4 && p.precision == PPP_FP64 && fits(2) ? 2 : 1;
+    }
     if (replicas <= 49152) return 4;
-    return replicas <= 131072 ? 2 : 1;
+    return replicas <= 98304 ? 2 : 1;
 }
 
 struct TuneEntry { int nmax, precision, G, B; };
@@ -267,7 +286,7 @@ ppp_status build_problem(const ppp_problem *p, ProblemHost &ph, const std::vecto
         ph.init.assign(1, p->init_coords ? p->init_coords[0] : p->lambda[0]);
         ph.G = 1; ph.B = 1;
         const int64_t sim_windows = (p->flags & PPP_FLAG_SEQUENTIAL) ? 1 : (int64_t)p->n_windows + ((p->flags & PPP_FLAG_FREE_ENSEMBLE) ? 1 : 0);
-        ph.lanes_1d = default_lanes_1d(sim_windows * p->n_replicas);
+        ph.lanes_1d = default_lanes_1d(*p, sim_windows);
     }
     ph.p.init_coords = ph.init.data();
     DevProblem &d = ph.dev;

@@ -291,12 +291,13 @@ template <int L> __device__ __forceinline__ double group_prefix_max(double a) {
 // f mod L of the group.
 constexpr int kOrderedSums = 6;
 
-// LDS of one workgroup: the (alpha, beta) of up to L samples per group.  Seven
+// LDS of one workgroup: the (alpha, beta) of up to L samples per group (none at one
+// lane a replica, which leaves the LDS to the histogram).  Seven
 // places of 16 bytes a lane for the six pairs, and six more between groups of 16
 // lanes, so that the lanes of a wavefront that read one sample's pairs for their
 // groups reach different banks.
-struct Lds1d {
-    double2 ab[WG * 7 + (WG / 16) * 6];
+template <int L> struct Lds1d {
+    double2 ab[L == 1 ? 1 : WG * 7 + (WG / 16) * 6];
 };
 template <int L> __device__ __forceinline__ int ab_place(int thread) { return thread * 7 + (L == 16 ? (thread >> 4) * 6 : 0); }
 
@@ -339,7 +340,7 @@ __device__ __forceinline__ uint32_t first_sample_1d(const DevProblem &P, int64_t
 template <typename T, int L, int POT>
 __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int rep, char *ws, int64_t step_begin,
                                                int64_t step_end, double *traj, int traj_rep, unsigned int *lhist,
-                                               Lds1d &lds) {
+                                               Lds1d<L> &lds) {
     const int l = (int)threadIdx.x & (L - 1);
     // record (window, replica); the sequential protocol keeps one state per replica
     // and draws replica `rep`'s window-1 noise all the way
@@ -464,7 +465,7 @@ __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int r
                 T eta = z[0];
 #pragma unroll
                 for (int q = 1; q < 4; ++q) eta = (k & 3u) == (uint32_t)q ? z[q] : eta;
-                eta = __shfl(eta, (int)(k >> 2), L);
+                if constexpr (L > 1) eta = __shfl(eta, (int)(k >> 2), L);
                 const T cen = pull_end > 0 ? (T)centre_at(P, lam_w, (int64_t)n - 1) : c_fix;
                 x = step_1d<T, POT>(x, c0, pb, cen, kr, mu_dt, amp, fma_t(w_prev, eta_prev, eta));
                 eta_prev = eta;
@@ -480,6 +481,47 @@ __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int r
         // fold the pending samples when the next tile's might not fit, and at the end
         if (cnt == 0 || (cnt + per_tile <= L && n < n_end && !traj)) continue;
         const double xi = (double)(qs < 2 ? (qs ? xs[1] : xs[0]) : (qs == 2 ? xs[2] : xs[3]));
+        if constexpr (L == 1) {
+            // One lane a replica: nothing to exchange.  The same sums as below, rounded
+            // alike, without the pairs, the ballots and the selects for lanes without a
+            // sample, which set the pace where a sample is taken every few steps: 344064
+            // replicas in fp32, a sample every step, 500 steps: 1.56 -> 1.18 ms (1.20 with
+            // a lane per replica and one step after another); every tenth 0.28 -> 0.23;
+            // with 16384 bins 0.88 -> 0.46.
+#pragma clang fp contract(off)
+            cnt = 0;
+            if (!alive) continue;
+            if (!isfinite(xi) || fabs(xi) > bound) {
+                x_dead = (T)xi;
+                eta_dead = qs < 2 ? (qs ? es[1] : es[0]) : (qs == 2 ? es[2] : es[3]);
+                acc[A_BLOWN] = 1.0;
+                alive = false;
+                continue;
+            }
+            auto fold = [&](int kind, double c, double h, double ref, double &m, double &S, double &S2) {
+                const double e = xi - ref;
+                const double a = kind == 1 ? c * (e - h) : c * e * e;
+                const double da = a - m, t = exp(-fabs(da)), t2 = t * t;
+                const bool up = da > 0.0;
+                S = up ? fma(S, t, 1.0) : S + t;
+                S2 = up ? fma(S2, t2, 1.0) : S2 + t2;
+                m = fmax(m, a);
+            };
+            const double d = xi - lam_w;
+            own[0] += d;
+            own[1] += d * d;
+            if (C.kind_f) fold(C.kind_f, cf, C.hf, ref_f, acc[A_MF], own[2], own[3]);
+            if (C.kind_r) fold(C.kind_r, cr, C.hr, ref_r, acc[A_MR], own[4], own[5]);
+            x_min = fmin(x_min, xi);
+            x_max = fmax(x_max, xi);
+            acc[A_N] += 1.0;
+            const double fb = floor((xi - xi_min) / xi_bin);
+            if (fb < 0.0) acc[A_UNDER] += 1.0;
+            else if (fb >= k_bins) acc[A_OVER] += 1.0;
+            else if (lhist) atomicAdd(lhist + (int)fb, 1u);
+            else atomicAdd(hist_w + (int64_t)fb, 1ull);
+            continue;
+        }
         const uint64_t bad = __ballot(l < cnt && (!isfinite(xi) || fabs(xi) > bound)) & group_mask;
         bool mine = l < cnt && alive;
         if (alive && bad) {
@@ -570,7 +612,7 @@ __global__ __launch_bounds__(WG) void sim_1d(const DevProblem *__restrict__ prob
                                              int n_items, char *__restrict__ ws, int64_t step_begin,
                                              int64_t step_end, double *__restrict__ traj, int traj_rep, int lds_cap) {
     extern __shared__ unsigned int s_hist[];
-    __shared__ Lds1d lds;
+    __shared__ Lds1d<L> lds;
     const int it = blockIdx.x;
     if (it >= n_items) return;
     const WorkItem item = items[it];
