@@ -12,7 +12,8 @@ int sim_blocks_per_cu(int precision, int G, int B, int lds_cap, bool wide);  // 
 // workgroup-private xi histograms: up to this many bins live in LDS (else counts go straight to memory)
 constexpr int kLdsHistCap = 16384;
 
-// wide: enough chain workgroups for three wavefronts a SIMD
+// chains: n_items items, shape G x B; wide: enough workgroups for three wavefronts a SIMD.
+// 1-D model: n_items runs of B replicas (a window's items, or one item), G lanes a replica.
 hipError_t launch_sim(const DevProblem *d_probs, const WorkItem *d_items, int n_items, char *ws, int64_t step_begin,
                       int64_t step_end, int model, int precision, int G, int B, double *traj, int64_t traj_rep,
                       int lds_cap, bool wide, hipStream_t stream);

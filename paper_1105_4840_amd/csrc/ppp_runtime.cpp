@@ -380,7 +380,7 @@ int64_t total_steps(const ProblemHost &ph) {
     return ph.dev.sequential ? (int64_t)ph.dev.n_windows * ph.dev.n_steps : ph.dev.n_steps;
 }
 
-int reps_per_item(const ProblemHost &ph) { return ph.dev.model == PPP_MODEL_CHAIN ? chain_reps_per_wg(ph.G) : WG / ph.lanes_1d; }
+int reps_per_item(const ProblemHost &ph) { return ph.dev.model == PPP_MODEL_CHAIN ? chain_reps_per_wg(ph.G) : WG; }
 
 // Work items of one problem.  Per window (every item inside one window), or,
 // for chain problems whose windows do not split into whole items, as runs of
@@ -495,8 +495,13 @@ ppp_status launch_items(ppp_handle *h, const ProblemHost &ph, int64_t b, int64_t
                         int64_t traj_rep, int first, int count) {
     const int64_t nk = (int64_t)ph.item_windows * ph.dev.xi_nbins;
     const int cap = nk <= kLdsHistCap ? (int)nk : 0;
-    const int G = ph.dev.model == PPP_MODEL_CHAIN ? ph.G : ph.lanes_1d;
-    const bool wide = ph.dev.model == PPP_MODEL_CHAIN && G == 64 && third_wave_pays(count, cap);
+    // the 1-D model: lanes a replica, and the replicas of a run: a window's, or one item's
+    const bool chain = ph.dev.model == PPP_MODEL_CHAIN;
+    const int G = chain ? ph.G : ph.lanes_1d;
+    const bool all = count == ph.n_items;
+    const int B = chain ? ph.B : all ? (int)ph.dev.n_replicas : h->items[first].n_reps;
+    const int n = chain || !all ? count : ph.dev.sequential ? 1 : ph.dev.n_sim_windows;
+    const bool wide = chain && G == 64 && third_wave_pays(count, cap);
     // sequential protocol: one launch per window touched, so a launch never
     // crosses a window boundary (the kernel takes the window from its first step);
     // parallel: no launch from step 0 to step 2^32 - 1 (the 1-D kernel's step numbers
@@ -505,8 +510,8 @@ ppp_status launch_items(ppp_handle *h, const ProblemHost &ph, int64_t b, int64_t
     int64_t at = b;
     do {
         const int64_t stop = std::min(e, (at / T + 1) * T);
-        HIPCHK(h, launch_sim(d_probs(h), d_items(h) + first, count, h->ws, at, stop, ph.dev.model, ph.dev.precision,
-                             G, ph.B, traj, traj_rep, cap, wide, st));
+        HIPCHK(h, launch_sim(d_probs(h), d_items(h) + first, n, h->ws, at, stop, ph.dev.model, ph.dev.precision,
+                             G, B, traj, traj_rep, cap, wide, st));
         at = stop;
     } while (at < e);
     return PPP_OK;

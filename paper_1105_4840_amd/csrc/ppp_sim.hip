@@ -59,11 +59,13 @@ hipError_t launch_sim(const DevProblem *d_probs, const WorkItem *d_items, int n_
                       int lds_cap, bool wide, hipStream_t stream) {
     if (n_items <= 0) return hipSuccess;
     if (model == 0) {
+        // the 1-D model: n_items runs of B replicas, G lanes each
         const size_t sh = (size_t)lds_cap * 4;
+        const dim3 grid(n_items * ((B + WG / G - 1) / (WG / G)));
 #define PPP_LAUNCH(L)                                                                                                   \
     if (G == L) {                                                                                                      \
-        if (precision == 1) hipLaunchKernelGGL((sim_1d<double, L>), dim3(n_items), dim3(WG), sh, stream, d_probs, d_items, n_items, ws, step_begin, step_end, traj, (int)traj_rep, lds_cap); \
-        else hipLaunchKernelGGL((sim_1d<float, L>), dim3(n_items), dim3(WG), sh, stream, d_probs, d_items, n_items, ws, step_begin, step_end, traj, (int)traj_rep, lds_cap); \
+        if (precision == 1) hipLaunchKernelGGL((sim_1d<double, L>), grid, dim3(WG), sh, stream, d_probs, d_items, n_items, B, ws, step_begin, step_end, traj, (int)traj_rep, lds_cap); \
+        else hipLaunchKernelGGL((sim_1d<float, L>), grid, dim3(WG), sh, stream, d_probs, d_items, n_items, B, ws, step_begin, step_end, traj, (int)traj_rep, lds_cap); \
         return hipGetLastError();                                                                                      \
     }
         PPP_LAUNCH(1) PPP_LAUNCH(2) PPP_LAUNCH(4) PPP_LAUNCH(8) PPP_LAUNCH(16)
