@@ -495,13 +495,12 @@ ppp_status launch_items(ppp_handle *h, const ProblemHost &ph, int64_t b, int64_t
                         int64_t traj_rep, int first, int count) {
     const int64_t nk = (int64_t)ph.item_windows * ph.dev.xi_nbins;
     const int cap = nk <= kLdsHistCap ? (int)nk : 0;
-    // the 1-D model: lanes a replica, and the replicas of a run: a window's, or one item's
+    // the 1-D model: the replicas of a run, a window's or one item's
     const bool chain = ph.dev.model == PPP_MODEL_CHAIN;
-    const int G = chain ? ph.G : ph.lanes_1d;
     const bool all = count == ph.n_items;
     const int B = chain ? ph.B : all ? (int)ph.dev.n_replicas : h->items[first].n_reps;
     const int n = chain || !all ? count : ph.dev.sequential ? 1 : ph.dev.n_sim_windows;
-    const bool wide = chain && G == 64 && third_wave_pays(count, cap);
+    const bool wide = chain && ph.G == 64 && third_wave_pays(count, cap);
     // sequential protocol: one launch per window touched, so a launch never
     // crosses a window boundary (the kernel takes the window from its first step);
     // parallel: no launch from step 0 to step 2^32 - 1 (the 1-D kernel's step numbers
@@ -510,6 +509,11 @@ ppp_status launch_items(ppp_handle *h, const ProblemHost &ph, int64_t b, int64_t
     int64_t at = b;
     do {
         const int64_t stop = std::min(e, (at / T + 1) * T);
+        // A launch of a few steps is bound by its records and takes most steps one by one:
+        // one lane a replica.  Advances of 1 / 8 / 16 / 33 steps, us each, 43008 replicas in
+        // fp32, one lane 13.9 / 15.5 / 16.7 / 18.9, four 14.9 / 17.3 / 19.8 / 21.0; 5376 in
+        // fp64, one 13.0 / 15.6 / 17.4 / 21.4, eight 13.0 / 15.4 / 17.2 / 20.3.
+        const int G = chain ? ph.G : stop - at <= 16 ? 1 : ph.lanes_1d;
         HIPCHK(h, launch_sim(d_probs(h), d_items(h) + first, n, h->ws, at, stop, ph.dev.model, ph.dev.precision,
                              G, B, traj, traj_rep, cap, wide, st));
         at = stop;

@@ -594,6 +594,13 @@ __device__ __forceinline__ void sim_1d_replica(const DevProblem &P, int w, int r
     }
     acc[A_MF2] = 2.0 * acc[A_MF]; acc[A_MR2] = 2.0 * acc[A_MR];
     acc[A_XMIN] = x_min; acc[A_XMAX] = x_max;
+    if constexpr (L == 1) {
+        // the whole record in one run of stores: an advance by single steps is bound by it
+        for (int f = 0; f < kOrderedSums; ++f) acc[kSumField[f]] = own[f];
+        for (int f = 0; f < A_NFIELDS; ++f) acc_g[f] = acc[f];
+        st[0] = alive ? x : x_dead; st[1] = alive ? eta_prev : eta_dead;
+        return;
+    }
     if (l == 0) {
         for (int f = 0; f < A_NFIELDS; ++f)
             if (f != A_S1 && f != A_S2 && f != A_SF && f != A_SF2 && f != A_SR && f != A_SR2) acc_g[f] = acc[f];
