@@ -333,7 +333,10 @@ const char *ppp_status_string(ppp_status s);
 const char *ppp_create_error(void);
 const char *ppp_last_error(const ppp_handle *h); /* NULL-safe; "" when no error */
 
-/* ---- parity hooks (same kernels as the run path) ------------------------ */
+/* ---- parity hooks --------------------------------------------------------
+ * Trajectories and noise come from the run path's own kernels.  Forces come from
+ * the same routine, compiled with energies; the fp32 runs of chains longer than 32
+ * beads take their Lennard-Jones rounds from assembly in the same arithmetic. */
 
 /* Energy and forces of n_rep configurations of h's system at restraint
  * centre lambda, computed by the simulation kernel's force routine in the

@@ -874,7 +874,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(1, chain_max
     }
 }
 
-// Energies and forces of configurations (parity hook): one group per configuration.
+// Energies and forces of configurations (parity hook): one group per configuration,
+// with the compiled rounds for every shape (those in assembly form no energies; one
+// step of theirs is held against the oracle instead).
 // The problem comes with the kernel's arguments: copied to the workspace before every
 // launch, with a wait for the copy, it was 19 of a small call's 30 us (256
 // configurations of ten beads, 7 us on the GPU; now 11 us).
