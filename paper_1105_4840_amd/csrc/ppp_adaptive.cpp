@@ -24,14 +24,14 @@ constexpr int kGrid = 1025;          // surrogate evaluation grid over the lambd
 constexpr int kMaxTrain = 4096;      // points per gradient launch
 
 struct MlpBuffers {
-    float *params, *grad, *m, *v, *loss;
+    float *params, *m, *v, *loss;
     float *t, *yv, *wv, *ys, *ws;    // training data [kMaxTrain]
     float *gt, *gy, *gdy;            // grid evaluation [kGrid]
 };
 
 int64_t mlp_bytes() {
     int64_t b = 0;
-    b += 4 * align_up(PPP_MLP_PARAMS * 4) + align_up(4);
+    b += 3 * align_up(PPP_MLP_PARAMS * 4) + align_up(4);
     b += 5 * align_up(kMaxTrain * 4);
     b += 3 * align_up(kGrid * 4);
     return b;
@@ -40,7 +40,7 @@ int64_t mlp_bytes() {
 MlpBuffers carve(char *p) {
     MlpBuffers m{};
     auto take = [&](int64_t bytes) { float *r = reinterpret_cast<float *>(p); p += align_up(bytes); return r; };
-    m.params = take(PPP_MLP_PARAMS * 4); m.grad = take(PPP_MLP_PARAMS * 4);
+    m.params = take(PPP_MLP_PARAMS * 4);
     m.m = take(PPP_MLP_PARAMS * 4); m.v = take(PPP_MLP_PARAMS * 4); m.loss = take(4);
     m.t = take(kMaxTrain * 4); m.yv = take(kMaxTrain * 4); m.wv = take(kMaxTrain * 4);
     m.ys = take(kMaxTrain * 4); m.ws = take(kMaxTrain * 4);
