@@ -48,15 +48,15 @@ TRAFFIC = {
                 "fetch_kib": 167.0, "fetch_scale": 1048576 / 524307.8125, "write_kib": 10145.71875,
                 "write_scale": 1048576 / 1048576.0},
 }
-KERNEL_SOURCES = ("ppp_sim_impl.hpp", "ppp_chain_force.hpp", "ppp_device.hpp", "ppp_internal.hpp", "ppp_sim.hip",
-                  "ppp_shapes.hpp", "ppp_launch.hpp")
+KERNEL_SOURCES = ("csrc/ppp_sim_impl.hpp", "csrc/ppp_chain_force.hpp", "csrc/ppp_device.hpp", "csrc/ppp_internal.hpp",
+                  "csrc/ppp_sim.hip", "csrc/ppp_shapes.hpp", "csrc/ppp_launch.hpp", "lj_rounds.py")
 
 
 def kernel_sources_digest():
     import hashlib
     h = hashlib.sha1()
     for name in KERNEL_SOURCES:
-        with open(os.path.join(ROOT, "paper_1105_4840_amd", "csrc", name), "rb") as f:
+        with open(os.path.join(ROOT, "paper_1105_4840_amd", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
 
