@@ -334,9 +334,10 @@ const char *ppp_create_error(void);
 const char *ppp_last_error(const ppp_handle *h); /* NULL-safe; "" when no error */
 
 /* ---- parity hooks --------------------------------------------------------
- * Trajectories and noise come from the run path's own kernels.  Forces come from
- * the same routine, compiled with energies; the fp32 runs of chains longer than 32
- * beads take their Lennard-Jones rounds from assembly in the same arithmetic. */
+ * Trajectories and noise come from the run path's own kernels.  Forces of chains come
+ * from the same routine, compiled with energies; the fp32 runs of chains longer than
+ * 32 beads take their Lennard-Jones rounds from assembly in the same arithmetic.  The
+ * 1-D model's forces are the same formula, fused into the step in the kernel. */
 
 /* Energy and forces of n_rep configurations of h's system at restraint
  * centre lambda, computed by the simulation kernel's force routine in the

@@ -43,11 +43,15 @@ __device__ __forceinline__ float unit_f32(uint32_t r) {
 // Box-Muller in fp64 on u = f 2^-BITS, f = integer + 1/2 below 2^BITS (exact).
 // The three functions it needs take arguments of one narrow kind here, so each
 // is a short polynomial without a library function's range checks: a block's two
-// pairs and its Philox words take 215 vector instructions, 359 with the
-// library's log, sqrt and sincospi, and the noise is half of the fp64 1-D
-// kernel's instructions.  Largest errors over 2e7 arguments, edges included, in
-// units of 2^-53 (relative; absolute for cos and sin): -2 ln u 2.0, sqrt 1.0,
-// cos and sin 1.8; the library's cos of the rounded product 2 pi u has 5.8.
+// pairs and its Philox words take 204 vector instructions, 354 with the
+// library's log, sqrt and sincospi, 866 with its log, sqrt, cos and sin (range
+// reduction included), and the noise is half of the fp64 1-D kernel's
+// instructions.  Largest errors over 2e7 arguments, edges included, in units of
+// 2^-53 (relative; absolute for cos and sin): -2 ln u 2.0 (a library's logarithm
+// has about 1), sqrt 1.0, cos and sin 1.8 (5.8 for the library's cos of the rounded
+// product 2 pi u).  A normal, against 64-bit mantissas over 8e6, relative to its
+// radius: 3.1 at most and 0.43 on average; 6.5 and 1.07 with the library's log,
+// sqrt, cos and sin.
 // ---------------------------------------------------------------------------
 
 // -2 ln u.  f = 2^k m with m in [sqrt(1/2), sqrt 2), ln m = 2 atanh s with s =

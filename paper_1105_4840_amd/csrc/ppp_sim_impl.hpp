@@ -237,8 +237,8 @@ template <typename T> __device__ __forceinline__ T *state_ptr(char *ws, const De
 // next tile's might not fit, and are then folded together, every lane evaluating
 // its sample's exponentials.  Only the sums that keep the samples' order are
 // serial: one fused product per sample, each sum on a lane of its own.  20000
-// steps of that workload in fp64: 12.3 ms at a lane per replica, 1.7 ms here;
-// 21 x 4096 replicas, 2000 steps: 1.75 and 0.67 ms.
+// steps of that workload in fp64: 12.3 ms at a lane per replica, 1.4 ms here;
+// 21 x 4096 replicas, 2000 steps: 1.75 and 0.65 ms.
 // ===========================================================================
 // Orders a wavefront's LDS accesses before and after it (its lanes exchange data
 // through LDS without a workgroup barrier; the hardware keeps one wavefront's LDS

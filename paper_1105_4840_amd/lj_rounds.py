@@ -25,9 +25,11 @@ bank); v_cmp and v_cndmask 3.2 each; v_rcp 8.2.  So:
 A pair's last instructions fall into the next round: the first round stands before the
 loop without them, and the last pairs are finished after it.
 
-The loop alone with GAP = 4, cycles a pair at 2 / 3 / 4 wavefronts a SIMD: the compiler's
-code for lj_block 77 / 69 / 65, these rounds 66 / 59 / 56.  GAP = 3, 5 and 6 inside the
-kernels: 256 beads -1.4, +1.3 and +1.3%; more pairs in flight cost registers.  The
+The loop alone, measured at GAP = 4, cycles a pair at 2 / 3 / 4 wavefronts a SIMD: the
+compiler's code for lj_block 77 / 69 / 65, these rounds 66 / 59 / 56.  Kernel times at
+GAP = 3 / 4 / 5 / 6, ms: 256 beads (21 windows of 4096, 30 steps) 37.5 / 36.9 / 36.6 /
+36.6, 128 beads (21 x 2048, 100 steps) 16.3 / 16.1 / 15.9 / 16.0, 64 beads (21 x 4096,
+150 steps) 13.4 / 13.2 / 13.1 / 13.1.  More pairs in flight cost registers.  The
 compiler schedules its loop with more registers inside the kernels, so there the gain
 comes with the third wavefront that the kernels using these rounds are built to fit:
 256 beads, 41 windows of 4096 replicas, 30 steps: 76.7 -> 71.2 ms (79.4 at two
