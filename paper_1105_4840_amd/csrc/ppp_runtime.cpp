@@ -510,10 +510,13 @@ ppp_status launch_items(ppp_handle *h, const ProblemHost &ph, int64_t b, int64_t
     do {
         const int64_t stop = std::min(e, (at / T + 1) * T);
         // A launch of a few steps is bound by its records and takes most steps one by one:
-        // one lane a replica.  Advances of 1 / 8 / 16 / 33 steps, us each, 43008 replicas in
-        // fp32, one lane 13.9 / 15.5 / 16.7 / 18.9, four 14.9 / 17.3 / 19.8 / 21.0; 5376 in
-        // fp64, one 13.0 / 15.6 / 17.4 / 21.4, eight 13.0 / 15.4 / 17.2 / 20.3.
-        const int G = chain ? ph.G : stop - at <= 16 ? 1 : ph.lanes_1d;
+        // one lane a replica.  Advances of 1 / 8 / 16 / 25 / 33 steps, us each: fp32, 43008
+        // replicas, one lane 13.9 / 15.5 / 16.7 / 17.6 / 18.9, four 14.9 / 17.3 / 19.8 / 20.2 /
+        // 21.0; 2100 replicas, one 12.0 / 13.5 / 14.8 / 15.8 / 17.1, sixteen 12.5 / 14.6 /
+        // 16.1 / 17.4 / 18.8; fp64, 252 replicas, one 12.1 / 15.0 / 17.5 / 19.9 / 22.4, sixteen
+        // 13.0 / 15.1 / 16.7 / 18.2 / 19.7.
+        const int few = ph.dev.precision == PPP_FP64 ? 16 : 32;
+        const int G = chain ? ph.G : stop - at <= few ? 1 : ph.lanes_1d;
         HIPCHK(h, launch_sim(d_probs(h), d_items(h) + first, n, h->ws, at, stop, ph.dev.model, ph.dev.precision,
                              G, B, traj, traj_rep, cap, wide, st));
         at = stop;
