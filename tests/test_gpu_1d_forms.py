@@ -57,3 +57,20 @@ def test_one_lane_and_sixteen_agree(precision, bins, every, pull):
         full = a[:, 15] == 0
         assert np.array_equal(a[full, 0], np.full(full.sum(), float(len(range(30 + every, 204, every)))))
         assert np.array_equal(a[:, 7], 2.0 * a[:, 5]) and np.array_equal(a[:, 11], 2.0 * a[:, 9])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_short_trajectories_are_the_start_of_long_ones(precision):
+    """A few steps run at one lane a replica, more at sixteen: the same positions."""
+    p = ppp_inputs.config_1d(n_replicas=131, n_steps=400, n_windows=3, seed=6, precision=precision)
+    p.update({"n_equil": 3, "sample_every": 4})
+    h = ppp.ppp_create(p)
+    try:
+        ws = ppp.workspace(h)
+        for window, replica in ((0, 0), (1, 130), (2, 77)):
+            long = ppp.ppp_trajectory(h, ws, window, replica, 400, 1).cpu().numpy()
+            for n in (1, 4, 16, 33):
+                short = ppp.ppp_trajectory(h, ws, window, replica, n, 1).cpu().numpy()
+                assert np.isfinite(short).all() and np.array_equal(short, long[:n + 1]), (window, replica, n)
+    finally:
+        ppp.ppp_destroy(h)
